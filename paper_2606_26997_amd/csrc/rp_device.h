@@ -48,6 +48,7 @@ enum : int {
   kHdrRespItems = 1,
   kHdrBigRespItems = 2,   // B-sized response items (they come first)
   kHdrRespChunkPages = 3,
+  kHdrClaim = 4,          // claims of the partial-attention launch (0 between launches)
   kHdrSlots = 16
 };
 // Largest group count the planner keeps in LDS.
@@ -198,6 +199,7 @@ constexpr int kQuadSwap1 = 0xB1;     // quad_perm [1,0,3,2]
 constexpr int kQuadSwap2 = 0x4E;     // quad_perm [2,3,0,1]
 constexpr int kRowHalfMirror = 0x141;
 constexpr int kRowMirror = 0x140;
+constexpr int kRowShl = 0x100;       // + n: lane i of a row of 16 reads lane i + n
 
 // Sum over aligned groups of N lanes (N in {4, 8, 16}); every lane of a group
 // gets the same, bitwise identical, total.

@@ -1,0 +1,92 @@
+"""Response units of the partial attention at the edges of a step (one, two or four pages, by head size
+and KV type), for every head ratio, in the precision the partial results are kept in: the fp32 partials
+are merged in fp64 and compared with the oracle, so that a lost term of the probabilities (bf16 alone
+would be 2^-9 of each) cannot hide behind the bf16 rounding of the output."""
+import copy
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from workloads import make_workload
+
+pytestmark = pytest.mark.gpu
+
+# Tokens around the ends of one, two and four pages, the first piece boundary (256 tokens) and beyond it.
+LENS = [1, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64, 65, 80, 81, 255, 256, 257, 300]
+SHAPES = [(nrep, d, dt) for nrep in (1, 2, 4, 8) for d in (64, 128) for dt in ("bf16", "fp8")]
+
+
+def _merged_partials(b):
+    """Output and lse of every query row from the planned workspace's fp32 partials, in fp64."""
+    import paper_2606_26997_amd as rp
+    b.plan()
+    b.attn_parts()
+    torch.cuda.synchronize()
+    info = rp._binding.plan_layout(b.kv, b.attn_layout)
+    S, Hq, d, n = b.q.shape[0], b.q.shape[1], b.q.shape[2], info.parts_per_row
+    ws = b.workspace.cpu().numpy()
+    po = ws[info.part_o:info.part_o + 4 * info.max_parts * d].view(np.float32).reshape(S, Hq, n, d).astype(np.float64)
+    pl = ws[info.part_lse:info.part_lse + 4 * info.max_parts].view(np.float32).reshape(S, Hq, n).astype(np.float64)
+    parts = b.plan_contents()["seq_parts"]
+    out, lse = np.zeros((S, Hq, d)), np.zeros((S, Hq))
+    for s in range(S):
+        p, o = pl[s, :, :parts[s]], po[s, :, :parts[s]]
+        lse[s] = np.logaddexp.reduce(p, axis=1)
+        out[s] = (np.exp(p - lse[s][:, None])[:, :, None] * o).sum(1)
+    return out, lse
+
+
+@pytest.mark.parametrize("nrep,d,dt", SHAPES)
+def test_partials_keep_fp32_precision(nrep, d, dt):
+    import paper_2606_26997_amd as rp
+    print(f"[case] steps nrep {nrep} d {d} {dt}", flush=True)
+    hkv = 3  # not a power of two, and not the eight that the XCD order divides by
+    wl = make_workload(num_q_heads=hkv * nrep, num_kv_heads=hkv, head_dim=d, seq_to_group=[0] * len(LENS),
+                       prefix_lens=[0], resp_lens=LENS, seed=nrep + d, kv_dtype=dt)
+    out, lse = _merged_partials(rp.DeviceBatch.from_workload(wl))
+    ref, ref_lse = oracle.attention_for_workload(wl)
+    absv = copy.copy(wl)
+    absv.v_pages = wl.v_pages & (0x7F if dt == "fp8" else 0x7FFF)
+    mag, _ = oracle.attention_for_workload(absv)  # sum p |v|
+    # fp32 rounding relative to sum p |v|: the dot product (sqrt(128) roundings of sum |q k| sigma ~ 7), the
+    # exponent's argument (at most 2^5) and the sums, about 1e-5 in all.
+    assert np.abs(lse - ref_lse).max() <= 3e-5
+    assert (np.abs(out - ref) / mag).max() <= 3e-5
+
+
+@pytest.mark.parametrize("nrep", [1, 2, 4, 8])
+def test_infinite_and_nan_values_stay_in_their_column(nrep):
+    import paper_2606_26997_amd as rp
+    print(f"[case] inf/nan nrep {nrep}", flush=True)
+    wl = make_workload(num_q_heads=2 * nrep, num_kv_heads=2, head_dim=128, seq_to_group=[0, 0], prefix_lens=[0],
+                       resp_lens=[40, 21], seed=5)
+    page = int(wl.resp_block_table[0, 1])
+    for col, bits in ((7, 0x7F80), (64, 0xFF80), (100, 0x7FC0)):
+        wl.v_pages[page, 1, 3, col] = bits
+    b = rp.DeviceBatch.from_workload(wl)
+    b.attention()
+    torch.cuda.synchronize()
+    out = b.out.float().cpu().numpy()
+    assert np.all(out[0, nrep:, 7] == np.inf) and np.all(out[0, nrep:, 64] == -np.inf)
+    assert np.isnan(out[0, nrep:, 100]).all()
+    out[0, nrep:, [7, 64, 100]] = 0
+    assert np.isfinite(out).all()
+
+
+@pytest.mark.parametrize("hkv,lens", [(1, [40] * 19), (2, [20] * 8), (8, [33] * 9), (3, [700, 16, 5])])
+def test_fp8_unit_order_covers_every_unit(hkv, lens):
+    """fp8 units are dealt eight items at a time; batches with a remainder of items, fewer than eight, and
+    kv-head counts that divide nothing."""
+    import paper_2606_26997_amd as rp
+    from tests.gpu_util import compare, to_host_out
+    print(f"[case] fp8 order hkv {hkv} items {len(lens)}", flush=True)
+    wl = make_workload(num_q_heads=2 * hkv, num_kv_heads=hkv, head_dim=128, seq_to_group=[0] * len(lens),
+                       prefix_lens=[18], resp_lens=lens, seed=hkv, kv_dtype="fp8")
+    b = rp.DeviceBatch.from_workload(wl)
+    b.workspace.fill_(0xFF)  # NaN partials: a unit left out shows
+    b.attention()
+    out, lse = to_host_out(b)
+    ref, ref_lse = oracle.attention_for_workload(wl)
+    compare(out, lse, ref, ref_lse, "fp8", f"order-{hkv}")
