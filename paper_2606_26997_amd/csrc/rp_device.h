@@ -48,7 +48,6 @@ enum : int {
   kHdrRespItems = 1,
   kHdrBigRespItems = 2,   // B-sized response items (they come first)
   kHdrRespChunkPages = 3,
-  kHdrClaim = 4,          // claims of the partial-attention launch (0 between launches)
   kHdrSlots = 16
 };
 // Largest group count the planner keeps in LDS.

@@ -150,7 +150,6 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
       v.hdr[kHdrRespItems] = nbig + incl;
       v.hdr[kHdrBigRespItems] = nbig;
       v.hdr[kHdrRespChunkPages] = chunk;
-      v.hdr[kHdrClaim] = 0;
     }
   }
 

@@ -50,9 +50,6 @@ __device__ inline int plan_piece_pages(const PlanArgs& a, long long W) {
   int chunk = kRespChunkStep * (int)min(max((W + unit / 2) / unit, 1ll), (long long)kRespChunkChoices);
   if (4 * W < 3 * unit && a.view.max_resp_chunks >= cdiv(a.max_resp_pages, kRespChunkPagesSmall))
     chunk = kRespChunkPagesSmall;
-#ifdef FORCEB
-  if (chunk > FORCEB) chunk = FORCEB;
-#endif
   return chunk;
 }
 
@@ -134,7 +131,6 @@ __device__ inline void plan_small(const PlanArgs& a, int* s_cnt) {
     v.hdr[kHdrRespItems] = nbig + nrag;
     v.hdr[kHdrBigRespItems] = nbig;
     v.hdr[kHdrRespChunkPages] = chunk;
-    v.hdr[kHdrClaim] = 0;
   }
 }
 
