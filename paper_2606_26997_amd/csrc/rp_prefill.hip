@@ -13,12 +13,6 @@
 // the n_rep query heads that share the kv-head, so every key block serves all
 // of them (details at the kernel). K/V are read from the projections (not
 // from the pool), as the prompt's own attention needs no quantised copy.
-//
-// Grid: workgroup b takes (group, kv-head) pair b % NP and row block
-// max_blocks - 1 - b / NP (the last rows, which see the most keys, first).
-// Workgroups are dealt to the 8 XCDs round-robin, so with NP a multiple of 8
-// every row block of a pair runs on one XCD and re-reads the pair's K/V from
-// that XCD's L2.
 #include "rp_device.h"
 #include "rp_internal.h"
 
@@ -107,168 +101,151 @@ __global__ __launch_bounds__(64) void prefill_kv_write_kernel(const PrefillArgs 
 // Workgroup of 4 waves on (group, kv-head) pair and a block of query rows:
 // wave w holds RT 16-row tiles (each 16 / n_rep consecutive prompt tokens
 // times the n_rep query heads of the kv-head), so a workgroup covers
-// 64 RT / n_rep tokens. Keys go through LDS in blocks of 32, double-buffered:
-// while the waves compute on one block, the next block's K and V (both
-// row-major, as in the projections) are loaded from the projections and
-// written into the other buffer; one barrier per
-// block. Per block and row tile: S^T = K Q^T on mfma 16x16x32 (Q stays in
-// registers), a causal mask, one online-softmax update per row, and
-// O^T += V^T P^T, also on mfma 16x16x32 (all 32 keys per instruction).
+// 64 RT / n_rep tokens. Keys go through LDS in blocks of 32, copied there
+// straight from the projections, with one barrier per block: two blocks ahead
+// in three stages with two row tiles (three workgroups per compute unit, by
+// registers and by LDS), one ahead in two stages with one (four). Per block
+// and row tile: S^T = K Q^T on mfma 16x16x32 (Q stays in registers), a causal
+// mask, one online-softmax update per row, and O^T += V^T P^T, also on mfma
+// 16x16x32 (all 32 keys per instruction).
+//
+// What bounds it: with short prompts HBM and the start of each workgroup (32
+// prompts of U[64, 512] tokens: 50 us, 3.0 TB/s with the pages), with long
+// ones the softmax beside the matrix products (8 prompts of 2048-4096 tokens:
+// 320 us, 1.0 PFLOP/s). Against staging through registers, the direct copies
+// measured 8% (1024 tokens: 4%), the maximum inside the product 4%, the mask
+// without a test for rows past the end 2%, and the order of pf_unit 12-20%.
 constexpr int kPfWaves = 4;
 constexpr int kPfThreads = 64 * kPfWaves;
 constexpr int kKeyBlk = 32;
 
-// Both K and V are staged row-major, as they come from the projections. The
-// V^T operand of P V is read with gfx950's transposing LDS read (lds_read_tr:
-// four rows of one column per lane).
+// A staged block holds K and V rows as they come from the projections, copied
+// by direct global-to-LDS loads: one instruction of one wave fills a 1 KiB
+// chunk of kRows rows. Row r lies in chunk r % kChunks, slot r / kChunks, and
+// chunks are 32 bytes more than 1 KiB apart, so that the eight rows of a
+// 16-byte K read and the four rows of a transposing V read lie in different
+// banks, at offsets that are immediates of the reads.
 template <int D>
 struct PfSmem {
-  static constexpr int kKPitch = D + 16;  // K rows, bf16: the 16-byte reads of 16 rows hit no bank twice
-  static constexpr int kVPitch = D + 16;  // V rows, bf16: 4 consecutive rows start 8 banks apart
-  static constexpr int kKElems = kKeyBlk * kKPitch;
-  static constexpr int kStage = kKElems + kKeyBlk * kVPitch;
-  static constexpr int kBytes = 2 * kStage * 2;
-  static constexpr int kChunks = kKeyBlk * D / 8;  // 16-byte pieces of a K (or V) block
-  static constexpr int kPerThread = kChunks / kPfThreads;
-  static_assert(kChunks % kPfThreads == 0, "block split");
-  static_assert(kPerThread == 1 || kPerThread == 2, "pieces per thread");
+  static constexpr int kRows = 512 / D;                 // rows per chunk
+  static constexpr int kChunks = kKeyBlk / kRows;       // chunks of a K (or V) block
+  static constexpr int kPitch = 512 + 16;               // bf16 elements between chunks
+  static constexpr int kElems = kChunks * kPitch;       // a K (or V) block
+  static constexpr int kStage = 2 * kElems;
+  static constexpr int kPerWave = 2 * kChunks / kPfWaves;  // copies per wave and block
+  static_assert(kChunks % kPfWaves == 0, "chunks per wave");
+  __device__ static constexpr int row(int r) { return (r % kChunks) * kPitch + (r / kChunks) * D; }
 };
-
-// This thread's share of one key block, in registers between the global
-// loads and the LDS writes. Clang vector types, not HIP's uint4: copies of
-// the latter go through memcpy and kept these values in scratch memory. Rows
-// at or past the prompt's end are read from its last token (inside the packed
-// arrays); their scores are masked.
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-struct PfBlock {
-  u32x4_t k0, k1, v0, v1;
-};
 
-// Byte offsets within one prompt's rows fit 32 bits (the host checks it), so
-// the loads take the group's wave-uniform base plus a 32-bit offset: no
-// 64-bit address arithmetic per block.
+// One direct global-to-LDS copy by a whole wave: 16 bytes per lane from
+// base + off to lds + 16 * lane. Written in assembly because the compiler
+// waits for every load in flight before any LDS read that follows its own
+// form of it; pf_wait waits for as many as are needed.
+__device__ inline void pf_copy(uint32_t lds, const uint16_t* base, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds), "v"(off), "s"(base)
+               : "memory");
+}
+// Waits until at most N of the wave's copies are in flight (and its LDS reads
+// are done), then for the workgroup's other waves.
+template <int N>
+__device__ inline void pf_wait() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+}
+
+// This wave's copies of one key block. Byte offsets within one prompt's rows
+// fit 32 bits (the host checks it). Rows at or past the prompt's end are read
+// from its last token (inside the packed arrays); their scores are masked.
 template <int D>
-__device__ inline void pf_load(const uint16_t* kbase, const uint16_t* vbase, uint32_t pitch, int u0, int last, int t,
-                               PfBlock& r) {
+__device__ inline void pf_load(uint32_t stage, const uint16_t* kbase, const uint16_t* vbase, uint32_t pitch, int u0,
+                               int last, int wave, int lane) {
   using L = PfSmem<D>;
-  const char* kb = reinterpret_cast<const char*>(kbase);
-  const char* vb = reinterpret_cast<const char*>(vbase);
-  {
-    const int key = t / (D / 8), col = (t - key * (D / 8)) * 8;
-    const uint32_t off = ((uint32_t)min(u0 + key, last) * pitch + (uint32_t)col) * 2u;
-    r.k0 = *reinterpret_cast<const u32x4_t*>(kb + off);
-    r.v0 = *reinterpret_cast<const u32x4_t*>(vb + off);
-  }
-  if constexpr (L::kPerThread == 2) {
-    const int c = t + kPfThreads;
-    const int key = c / (D / 8), col = (c - key * (D / 8)) * 8;
-    const uint32_t off = ((uint32_t)min(u0 + key, last) * pitch + (uint32_t)col) * 2u;
-    r.k1 = *reinterpret_cast<const u32x4_t*>(kb + off);
-    r.v1 = *reinterpret_cast<const u32x4_t*>(vb + off);
+  const int slot = lane / (D / 8), col = (lane % (D / 8)) * 8;
+#pragma unroll
+  for (int i = 0; i < L::kPerWave / 2; ++i) {
+    const int chunk = wave * (L::kPerWave / 2) + i;
+    const uint32_t off = ((uint32_t)min(u0 + slot * L::kChunks + chunk, last) * pitch + (uint32_t)col) * 2u;
+    pf_copy(stage + (uint32_t)(chunk * L::kPitch * 2), kbase, off);
+    pf_copy(stage + (uint32_t)((L::kElems + chunk * L::kPitch) * 2), vbase, off);
   }
 }
 
-template <int D>
-__device__ inline void pf_store(uint16_t* stage, int t, const PfBlock& r) {
-  using L = PfSmem<D>;
-  uint16_t* vst = stage + L::kKElems;
-  {
-    const int key = t / (D / 8), col = (t - key * (D / 8)) * 8;
-    *reinterpret_cast<u32x4_t*>(stage + key * L::kKPitch + col) = r.k0;
-    *reinterpret_cast<u32x4_t*>(vst + key * L::kVPitch + col) = r.v0;
+// Which (group, kv-head) pair and row block a workgroup takes. Workgroups are
+// dealt to the 8 XCDs round-robin, so with NP a multiple of 8 all row blocks
+// of a pair run on one XCD, and the order keeps few pairs at a time there:
+// kPfPairs of them, their row blocks interleaved, the last rows (which see the
+// most keys) first. Their keys then stay in the XCD's L2 (all pairs at once:
+// 1024-token prompts 239 us against 198, 2048-4096 tokens 366 against 320). An
+// XCD deals its workgroups to its shader engines in turn as well: an odd
+// number of pairs and an odd `stride` from one set of pairs to the next (one
+// idle workgroup where needed) keep a pair, or a row block, from falling to
+// one engine every time (4 pairs instead of 5 on ragged prompts of 300-1800
+// tokens: 317 us against 208). stride = 0: any NP, pairs dealt in turn.
+constexpr int kPfPairs = 5;
+__host__ __device__ inline int pf_stride(int max_blocks) { return (kPfPairs * max_blocks) | 1; }
+__device__ inline bool pf_unit(int b, int NP, int max_blocks, int stride, int* pair, int* rb) {
+  if (stride == 0) {
+    *pair = b % NP;
+    *rb = max_blocks - 1 - b / NP;
+    return true;
   }
-  if constexpr (L::kPerThread == 2) {
-    const int c = t + kPfThreads;
-    const int key = c / (D / 8), col = (c - key * (D / 8)) * 8;
-    *reinterpret_cast<u32x4_t*>(stage + key * L::kKPitch + col) = r.k1;
-    *reinterpret_cast<u32x4_t*>(vst + key * L::kVPitch + col) = r.v1;
-  }
+  const int i = b / 8, set = i / stride, r = i - set * stride;
+  const int m = min(kPfPairs, NP / 8 - set * kPfPairs);  // pairs of this set
+  *rb = max_blocks - 1 - r / m;
+  *pair = (set * kPfPairs + r % m) * 8 + b % 8;
+  return *rb >= 0;
 }
 
 // The one-launch prefill of a bf16 pool writes every prompt token's K/V rows
 // into the group's prefix pages from the workgroup whose query rows hold the
-// token (exactly one), in one of two ways; rows past the prompt's end are not
-// written, as in the page-write kernel.
-//
-// With one row tile per wave, the workgroup writes a key block's staged
-// registers (after they went to LDS) when the block starts with one of its
-// tokens. With two row tiles, the page addresses held across the key loop
-// would cost the kernel its third wave per SIMD (178 VGPRs), so the workgroup
-// copies its own rows in the prologue instead: the copy's loads are issued
-// together with the q rows and the first key block, and its stores follow
-// them (1024-token prompts 296 -> 280 us; with one row tile the prologue
-// copy was 5% slower on config-2 prompts, U[64, 512] tokens).
+// token (exactly one), once its attention is done: the rows are then in this
+// XCD's L2, and no register or wait of the key loop is spent on them. Rows
+// past the prompt's end are not written, as in the page-write kernel.
 template <int D, int TPB>
-struct PfOwnRows {
-  static constexpr int kCh = TPB * (D / 8);  // 16-byte pieces of the workgroup's rows (K or V)
-  static constexpr int kPer = (kCh + kPfThreads - 1) / kPfThreads;
-  u32x4_t k[kPer], v[kPer];
-
-  __device__ inline void load(int T0, int last, int t, const uint16_t* kbase, const uint16_t* vbase, uint32_t pitch) {
-    const char* kb = reinterpret_cast<const char*>(kbase);
-    const char* vb = reinterpret_cast<const char*>(vbase);
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int c = t + i * kPfThreads, tok = c / (D / 8), col = (c - tok * (D / 8)) * 8, u = T0 + tok;
-      if (c < kCh && u <= last) {
-        const uint32_t off = ((uint32_t)u * pitch + (uint32_t)col) * 2u;
-        k[i] = *reinterpret_cast<const u32x4_t*>(kb + off);
-        v[i] = *reinterpret_cast<const u32x4_t*>(vb + off);
-      }
-    }
-  }
-
-  __device__ inline void store(const PrefillArgs& a, int g, int h, int T0, int last, int t) const {
-    const int* pbt = a.prefix_block_table + (size_t)g * a.max_prefix_pages;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int c = t + i * kPfThreads, tok = c / (D / 8), col = (c - tok * (D / 8)) * 8, u = T0 + tok;
-      if (c < kCh && u <= last) {
-        const int page = clamp_page(pbt[u / kPage], a.num_pages);
-        const size_t off = (((size_t)page * a.num_kv_heads + h) * kPage + (u % kPage)) * D + col;
-        *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(a.k_pages) + off) = k[i];
-        *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(a.v_pages) + off) = v[i];
-      }
-    }
-  }
-};
-
-template <int D>
-__device__ inline void pf_write_pages(const PrefillArgs& a, int g, int h, int u0, int last, int t,
-                                      const PfBlock& r) {
-  using L = PfSmem<D>;
+__device__ inline void pf_write_pages(const PrefillArgs& a, int g, int h, int T0, int last, int t,
+                                      const uint16_t* kbase, const uint16_t* vbase, uint32_t pitch) {
+  constexpr int kPieces = TPB * (D / 8);  // 16-byte pieces of the workgroup's rows (K or V)
   const int* pbt = a.prefix_block_table + (size_t)g * a.max_prefix_pages;
-  uint16_t* kp = static_cast<uint16_t*>(a.k_pages);
-  uint16_t* vp = static_cast<uint16_t*>(a.v_pages);
-  const auto put = [&](int c, const u32x4_t& kk, const u32x4_t& vv) __attribute__((always_inline)) {
-    const int key = c / (D / 8), col = (c - key * (D / 8)) * 8, u = u0 + key;
-    if (u > last) return;
+#pragma unroll
+  for (int i = 0; i < (kPieces + kPfThreads - 1) / kPfThreads; ++i) {
+    const int c = t + i * kPfThreads, col = (c % (D / 8)) * 8, u = T0 + c / (D / 8);
+    if (c >= kPieces || u > last) continue;
+    const size_t src = (size_t)u * pitch + col;
     const int page = clamp_page(pbt[u / kPage], a.num_pages);
-    const size_t off = (((size_t)page * a.num_kv_heads + h) * kPage + (u % kPage)) * D + col;
-    *reinterpret_cast<u32x4_t*>(kp + off) = kk;
-    *reinterpret_cast<u32x4_t*>(vp + off) = vv;
-  };
-  put(t, r.k0, r.v0);
-  if constexpr (L::kPerThread == 2) put(t + kPfThreads, r.k1, r.v1);
+    const size_t dst = (((size_t)page * a.num_kv_heads + h) * kPage + (u % kPage)) * D + col;
+    *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(a.k_pages) + dst) = *reinterpret_cast<const u32x4_t*>(kbase + src);
+    *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(a.v_pages) + dst) = *reinterpret_cast<const u32x4_t*>(vbase + src);
+  }
 }
-
 
 // One 32-key block from LDS stage `kst` (keys u0 .. u0 + 31) for this wave's
 // RT row tiles: the scores of both 16-key sub-tiles, the causal mask, one
 // online-softmax update per row for the whole block, then O^T += V^T P^T.
-// A row's running maximum moves only when a block exceeds it by more than
-// kLazyMax; the accumulator is rescaled only when some row's maximum moved
-// (alpha is exactly 1 otherwise), a test uniform over the wave. MASK = false for
-// blocks that lie wholly at or below the diagonal of every row of the wave.
+// The products start from minus the row's running maximum (mneg, in raw
+// scores), so a block needs no cross-lane step unless some score exceeds that
+// maximum by more than thr (kLazyMax in log2 units; minus infinity until the
+// row has a maximum): then the maximum moves and the accumulator is rescaled.
+// MASK = false for blocks that lie wholly at or below the diagonal of every
+// row of the wave.
 template <int D, int NREP, int RT, bool MASK>
-__device__ __forceinline__ void pf_compute(const uint16_t* kst, int u0, int last, float qk_scale, int r16, int quad,
-                                           const int (&tr)[RT], const bf16x8_t (&qop)[RT][D / 32],
-                                           f32x4_t (&oacc)[RT][D / 16], float (&mrow)[RT], float (&lrow)[RT]) {
+__device__ __forceinline__ void pf_compute(const uint16_t* kst, int u0, float qk_scale, float thr_set, int r16,
+                                           int quad, const int (&tr)[RT], const bf16x8_t (&qop)[RT][D / 32],
+                                           f32x4_t (&oacc)[RT][D / 16], f32x4_t (&mneg)[RT], float (&thr)[RT],
+                                           float (&lrow)[RT]) {
   using L = PfSmem<D>;
   constexpr int KB = D / 32, DT = D / 16, ST = kKeyBlk / 16;
-  const uint16_t* vst = kst + L::kKElems;
+  const uint16_t* vst = kst + L::kElems;
   // Entry i of sub-tile st: key u0 + st*16 + quad*4 + i against row r16.
   f32x4_t sacc[RT][ST];
+  bf16x8_t kop[ST][KB];
+#pragma unroll
+  for (int st = 0; st < ST; ++st)
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+      kop[st][kb] = __builtin_bit_cast(
+          bf16x8_t, *reinterpret_cast<const uint4*>(kst + L::row(r16) + L::row(st * 16) + kb * 32 + quad * 8));
   // The waves of a SIMD come from different workgroups and drift in and out
   // of phase; raising the priority of a wave while it issues its MFMAs lets
   // another wave's softmax fill the matrix core's shadow instead of
@@ -278,67 +255,64 @@ __device__ __forceinline__ void pf_compute(const uint16_t* kst, int u0, int last
 #pragma unroll
   for (int st = 0; st < ST; ++st) {
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) sacc[rt][st] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int rt = 0; rt < RT; ++rt) sacc[rt][st] = mneg[rt];
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-      const bf16x8_t kop = __builtin_bit_cast(
-          bf16x8_t, *reinterpret_cast<const uint4*>(kst + (st * 16 + r16) * L::kKPitch + kb * 32 + quad * 8));
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) sacc[rt][st] = mfma16x16x32(kop, qop[rt][kb], sacc[rt][st]);
-    }
+      for (int rt = 0; rt < RT; ++rt) sacc[rt][st] = mfma16x16x32(kop[st][kb], qop[rt][kb], sacc[rt][st]);
   }
   __builtin_amdgcn_s_setprio(0);
-  // V^T operands are read inside P V, one 16-column tile at a time: fewer
-  // live registers than reading the whole block's ahead of the softmax,
-  // which keeps four waves per SIMD with one row tile and three with two.
-  const uint16_t* vtr = vst + (quad * 4 + r16 / 4) * L::kVPitch + 4 * (r16 % 4);
+  const uint16_t* vtr = vst + L::row(quad * 4 + r16 / 4) + 4 * (r16 % 4);
   const auto read_vop = [&](int dt) __attribute__((always_inline)) {
     const bf16x4_t v0 = lds_read_tr(vtr + dt * 16);
-    const bf16x4_t v1 = lds_read_tr(vtr + 16 * L::kVPitch + dt * 16);
+    const bf16x4_t v1 = lds_read_tr(vtr + L::row(16) + dt * 16);
     return __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
   };
+  // With one row tile per wave there are registers to request the V^T
+  // operands ahead of the softmax; with two they are read inside P V, one
+  // 16-column tile at a time, which keeps three waves per SIMD.
+  bf16x8_t vpre[DT];
+  if constexpr (RT == 1) {
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) vpre[dt] = read_vop(dt);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   bf16x4_t pop[RT][ST];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    // Raw scores (masked to -inf); the scale is applied inside the exponent,
-    // max(s * c) = max(s) * c for c > 0.
-    float x[ST][4];
-    float mloc = -INFINITY;
+    float mx = -INFINITY;
 #pragma unroll
     for (int st = 0; st < ST; ++st)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        if constexpr (MASK) {
-          const int u = u0 + st * 16 + quad * 4 + i;
-          x[st][i] = (tr[rt] <= last && u <= tr[rt]) ? sacc[rt][st][i] : -INFINITY;
-        } else {
-          x[st][i] = sacc[rt][st][i];
-        }
-        mloc = fmaxf(mloc, x[st][i]);
+        // Rows past the prompt's end need no mask: they are not stored.
+        if constexpr (MASK) sacc[rt][st][i] = st * 16 + i <= tr[rt] - u0 - quad * 4 ? sacc[rt][st][i] : -INFINITY;
+        mx = fmaxf(mx, sacc[rt][st][i]);
       }
-    mloc = max_xor16_32(mloc) * qk_scale;
-    // The running maximum moves only when this block exceeds it by more than
-    // kLazyMax (log2 units): the probabilities then stay below 2^kLazyMax,
-    // and most blocks leave the accumulator unscaled (alpha = exp2(0) = 1).
-    const float mnew = mloc > mrow[rt] + kLazyMax ? mloc : mrow[rt];
-    const float mu = mnew == -INFINITY ? 0.f : mnew;
-    const float alpha = fast_exp2(mrow[rt] - mu);
-    mrow[rt] = mnew;
+    if (__any(mx > thr[rt])) {
+      mx = max_xor16_32(mx);
+      const float up = mx > thr[rt] ? mx : 0.f;
+      // A row's first maximum may be far below zero: nothing to rescale yet.
+      const float alpha = thr[rt] == -INFINITY ? 0.f : fast_exp2(-up * qk_scale);
+      thr[rt] = mx > thr[rt] ? thr_set : thr[rt];
+      mneg[rt] -= up;
+      lrow[rt] *= alpha;
+#pragma unroll
+      for (int st = 0; st < ST; ++st) sacc[rt][st] -= up;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) oacc[rt][dt] *= alpha;
+    }
     float psum = 0.f;
 #pragma unroll
     for (int st = 0; st < ST; ++st) {
       float pw[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) pw[i] = fast_exp2(fmaf(x[st][i], qk_scale, -mu));
+      for (int i = 0; i < 4; ++i) pw[i] = fast_exp2(sacc[rt][st][i] * qk_scale);
       psum += (pw[0] + pw[1]) + (pw[2] + pw[3]);
       pop[rt][st] =
           __builtin_bit_cast(bf16x4_t, make_uint2(pack_bf16x2(pw[0], pw[1]), pack_bf16x2(pw[2], pw[3])));
     }
-    lrow[rt] = lrow[rt] * alpha + psum;
-    if (__any(alpha != 1.f)) {
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) oacc[rt][dt] *= alpha;
-    }
+    lrow[rt] += psum;
   }
   // O^T += V^T P^T over all 32 keys in one mfma 16x16x32 per 16 output
   // columns: lane (r16, quad) supplies contraction slots 8 quad .. 8 quad + 7,
@@ -355,7 +329,7 @@ __device__ __forceinline__ void pf_compute(const uint16_t* kst, int u0, int last
   __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
-    const bf16x8_t vo = read_vop(dt);
+    const bf16x8_t vo = RT == 1 ? vpre[dt] : read_vop(dt);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) oacc[rt][dt] = mfma16x16x32(vo, pop8[rt], oacc[rt][dt]);
   }
@@ -366,19 +340,20 @@ __device__ __forceinline__ void pf_compute(const uint16_t* kst, int u0, int last
 // VGPRs), two row tiles three (168 VGPRs).
 template <int D, int NREP, int RT, bool WP>
 __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(RT == 1 ? 4 : 3, 8)))
-void prefill_attn_kernel(const PrefillArgs a, int max_blocks) {
+void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride) {
   using L = PfSmem<D>;
   constexpr int KB = D / 32;              // MFMA k-blocks over head_dim
   constexpr int DT = D / 16;              // 16-column output tiles
   constexpr int TPT = 16 / NREP;          // prompt tokens per 16-row tile
   constexpr int TPW = RT * TPT;           // prompt tokens per wave
   constexpr int TPB = kPfWaves * TPW;     // prompt tokens per workgroup
-  __shared__ __attribute__((aligned(16))) uint16_t smem[L::kBytes / 2];
+  constexpr int STAGES = RT == 2 ? 3 : 2;
+  __shared__ __attribute__((aligned(16))) uint16_t smem[STAGES * L::kStage];
 
   const int Hkv = a.num_kv_heads, Hq = a.num_q_heads;
   const int NP = a.num_groups * Hkv;
-  const int pair = (int)(blockIdx.x % (unsigned)NP);
-  const int rb = max_blocks - 1 - (int)(blockIdx.x / (unsigned)NP);
+  int pair, rb;
+  if (!pf_unit((int)blockIdx.x, NP, max_blocks, stride, &pair, &rb)) return;
   const int g = pair / Hkv, h = pair - g * Hkv;
   int first;
   const int P = prompt_len(a, g, &first);
@@ -389,10 +364,6 @@ void prefill_attn_kernel(const PrefillArgs a, int max_blocks) {
   const size_t qpitch = (size_t)Hq * D, kpitch = (size_t)Hkv * D;
   const uint16_t* kbase = static_cast<const uint16_t*>(a.k) + (size_t)first * kpitch + (size_t)h * D;
   const uint16_t* vbase = static_cast<const uint16_t*>(a.v) + (size_t)first * kpitch + (size_t)h * D;
-
-  constexpr bool kOwnCopy = WP && RT == 2, kBlockWrite = WP && RT == 1;
-  PfOwnRows<D, TPB> own;
-  if constexpr (kOwnCopy) own.load(T0, last, t, kbase, vbase, (uint32_t)kpitch);
 
   // Row r16 of row tile rt: token T0 + wave * TPW + rt * TPT + r16 / NREP,
   // query head h * NREP + r16 % NREP. Q is the B operand of S^T = K Q^T.
@@ -410,41 +381,56 @@ void prefill_attn_kernel(const PrefillArgs a, int max_blocks) {
   }
 
   const int tlast = min(T0 + TPB, P) - 1;  // the workgroup's last token bounds its keys
-  const int w_first = T0 + wave * TPW, w_last = w_first + TPW - 1;  // this wave's tokens
+  const int w_first = T0 + wave * TPW;  // this wave's first token
   const int nblk = tlast / kKeyBlk + 1;
-  float mrow[RT], lrow[RT];
+  const float thr_set = kLazyMax / a.qk_scale;
+  float thr[RT], lrow[RT];
+  f32x4_t mneg[RT];
   f32x4_t oacc[RT][DT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    mrow[rt] = -INFINITY;
+    thr[rt] = -INFINITY;
+    mneg[rt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     lrow[rt] = 0.f;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) oacc[rt][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 
-  // The next block's loads are issued before this block's compute and
-  // written to the other LDS buffer after it (past the last block they read
-  // clamped rows and are never used).
-  PfBlock nx;
-  pf_load<D>(kbase, vbase, (uint32_t)kpitch, 0, last, t, nx);
-  if constexpr (kOwnCopy) own.store(a, g, h, T0, last, t);
-  pf_store<D>(smem, t, nx);
-  if (kBlockWrite && T0 == 0) pf_write_pages<D>(a, g, h, 0, last, t, nx);
-  __syncthreads();
+  // At a block's start its copies are complete (the wave's own, then, past
+  // the barrier, everyone's); with three stages the next block's are in
+  // flight, and the one after that is requested into the stage the barrier
+  // has freed.
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)smem;
+  const int uwave = __builtin_amdgcn_readfirstlane(wave);
+  const auto request = [&](int blk, int stage) __attribute__((always_inline)) {
+    pf_load<D>(lds0 + (uint32_t)(stage * L::kStage * 2), kbase, vbase, (uint32_t)kpitch, blk * kKeyBlk, last, uwave,
+               lane);
+  };
+  request(0, 0);
+  // The compiler's wait for the q rows belongs here: it does not count the
+  // copies, so inside the loop it would drain them in every block.
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(qop[rt][kb]));
+  if (STAGES == 3 && nblk > 1) request(1, 1);
+  int cur = 0;
   for (int blk = 0; blk < nblk; ++blk) {
-    pf_load<D>(kbase, vbase, (uint32_t)kpitch, (blk + 1) * kKeyBlk, last, t, nx);
-    // Blocks wholly below the diagonal for every (valid) row of the wave skip the mask.
-    if ((blk + 1) * kKeyBlk - 1 <= w_first && w_last <= last)
-      pf_compute<D, NREP, RT, false>(smem + (blk & 1) * L::kStage, blk * kKeyBlk, last, a.qk_scale, r16, quad, tr,
-                                     qop, oacc, mrow, lrow);
+    if (STAGES == 3 && blk + 1 < nblk) pf_wait<L::kPerWave>();
+    else pf_wait<0>();
+    if (blk + STAGES - 1 < nblk) request(blk + STAGES - 1, cur == 0 ? STAGES - 1 : cur - 1);
+    const uint16_t* kst = smem + cur * L::kStage;
+    // Blocks wholly below the diagonal for every row of the wave skip the mask.
+    if ((blk + 1) * kKeyBlk - 1 <= w_first)
+      pf_compute<D, NREP, RT, false>(kst, blk * kKeyBlk, a.qk_scale, thr_set, r16, quad, tr, qop, oacc, mneg, thr,
+                                     lrow);
     else
-      pf_compute<D, NREP, RT, true>(smem + (blk & 1) * L::kStage, blk * kKeyBlk, last, a.qk_scale, r16, quad, tr,
-                                    qop, oacc, mrow, lrow);
-    pf_store<D>(smem + ((blk + 1) & 1) * L::kStage, t, nx);
-    const int un = (blk + 1) * kKeyBlk;
-    if (kBlockWrite && un >= T0 && un < T0 + TPB) pf_write_pages<D>(a, g, h, un, last, t, nx);
-    __syncthreads();  // the next block is staged; this block's buffer may be overwritten next
+      pf_compute<D, NREP, RT, true>(kst, blk * kKeyBlk, a.qk_scale, thr_set, r16, quad, tr, qop, oacc, mneg, thr,
+                                    lrow);
+    cur = cur == STAGES - 1 ? 0 : cur + 1;
   }
+
+  if constexpr (WP) pf_write_pages<D, TPB>(a, g, h, T0, last, t, kbase, vbase, (uint32_t)kpitch);
 
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
@@ -457,7 +443,8 @@ void prefill_attn_kernel(const PrefillArgs a, int max_blocks) {
       const f32x4_t v = oacc[rt][dt] * inv;
       *reinterpret_cast<uint2*>(orow + dt * 16) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
     }
-    if (a.lse != nullptr && quad == 0) a.lse[(size_t)(first + tr[rt]) * Hq + jr] = (mrow[rt] + fast_log2(lt)) * kLn2;
+    if (a.lse != nullptr && quad == 0)
+      a.lse[(size_t)(first + tr[rt]) * Hq + jr] = (fast_log2(lt) - mneg[rt][0] * a.qk_scale) * kLn2;
   }
 }
 
@@ -471,15 +458,20 @@ hipError_t attn_launch(const PrefillArgs& a, hipStream_t st) {
   const int rt = (long long)a.num_tokens >= 384ll * a.num_groups ? 2 : 1;
   const int tpb = kPfWaves * rt * (16 / NREP);
   const int max_blocks = cdiv(max_tokens, tpb);
-  const long long blocks = NP * max_blocks;
+  // A launch has at most 2^24 workgroups of 256 threads; the idle ones of the
+  // ordered grid must not be what exceeds it.
+  const int stride = NP % 8 == 0 && NP * (max_blocks + 1) < (1ll << 24) ? pf_stride(max_blocks) : 0;
+  const long long pairs = NP / 8;
+  const long long blocks =
+      stride == 0 ? NP * max_blocks : 8 * (pairs / kPfPairs * stride + pairs % kPfPairs * max_blocks);
   if (blocks <= 0) return hipSuccess;
   const dim3 grid((unsigned)blocks), block(kPfThreads);
   if (a.write_pages) {
-    if (rt == 2) prefill_attn_kernel<D, NREP, 2, true><<<grid, block, 0, st>>>(a, max_blocks);
-    else prefill_attn_kernel<D, NREP, 1, true><<<grid, block, 0, st>>>(a, max_blocks);
+    if (rt == 2) prefill_attn_kernel<D, NREP, 2, true><<<grid, block, 0, st>>>(a, max_blocks, stride);
+    else prefill_attn_kernel<D, NREP, 1, true><<<grid, block, 0, st>>>(a, max_blocks, stride);
   } else {
-    if (rt == 2) prefill_attn_kernel<D, NREP, 2, false><<<grid, block, 0, st>>>(a, max_blocks);
-    else prefill_attn_kernel<D, NREP, 1, false><<<grid, block, 0, st>>>(a, max_blocks);
+    if (rt == 2) prefill_attn_kernel<D, NREP, 2, false><<<grid, block, 0, st>>>(a, max_blocks, stride);
+    else prefill_attn_kernel<D, NREP, 1, false><<<grid, block, 0, st>>>(a, max_blocks, stride);
   }
   return hipGetLastError();
 }

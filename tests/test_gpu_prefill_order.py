@@ -1,0 +1,70 @@
+"""Prefill grids: the order that keeps few (group, kv-head) pairs on an XCD at a time, its remainders, and
+the plain order of pair counts that are no multiple of 8; prompts around the ends of key blocks and
+workgroup rows, one and two row tiles per wave. Every row is compared with the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from workloads import make_prefill_workload
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (name, Hq, Hkv, d, prompt lengths, kv dtype)
+    ("one-set", 16, 8, 128, [33, 64, 31], "bf16"),                       # 3 of 5 pairs per XCD
+    ("two-sets-odd-blocks", 16, 8, 64, [95, 1, 32, 65, 96, 17], "bf16"),  # 5 + 1 pairs, 3 row blocks
+    ("two-sets-even-blocks", 8, 8, 128, [128, 127, 0, 63, 64, 3, 100], "bf16"),
+    ("half-pairs", 16, 4, 128, [40, 16, 70, 8], "fp8"),                  # 16 pairs from 4 kv-heads
+    ("plain-order", 4, 2, 128, [50, 33, 130], "bf16"),                   # 6 pairs
+    ("plain-order-nrep8", 8, 1, 64, [20, 45, 64], "bf16"),
+    ("two-tiles", 16, 8, 128, [400, 385, 31, 800], "bf16"),              # 404 tokens a prompt
+    ("two-tiles-nrep8", 32, 4, 128, [390, 417, 500, 400], "bf16"),
+    ("two-tiles-plain", 6, 3, 64, [410, 390], "fp8"),
+    ("two-tiles-mha", 8, 8, 64, [641, 129], "bf16"),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_every_row_of_every_order(case):
+    import paper_2606_26997_amd as rp
+    name, hq, hkv, d, lens, dt = case
+    print(f"[case] prefill order {name}", flush=True)
+    w = make_prefill_workload(num_q_heads=hq, num_kv_heads=hkv, head_dim=d, prefix_lens=lens, seed=len(name),
+                              kv_dtype=dt)
+    b = rp.PrefillBatch.from_workload(w)
+    b.out.fill_(float("nan"))
+    b.lse.fill_(float("nan"))
+    b.prefill()
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle.prefill_attention(w.q, w.k, w.v, w.prefix_offs, w.softmax_scale)
+    out, lse = b.out.float().cpu().numpy().astype(np.float64), b.lse.cpu().numpy().astype(np.float64)
+    # The bf16 output's own rounding (half an ulp of each exact value) plus the contract's bound.
+    half_ulp = np.ldexp(1.0, np.frexp(np.abs(ref))[1] - 9)
+    assert np.maximum(np.abs(out - ref) - half_ulp, 0).max() <= 1e-2
+    assert np.linalg.norm(out - ref) <= 5e-3 * np.linalg.norm(ref)
+    assert np.abs(lse - ref_lse).max() <= 1e-4
+
+
+def test_large_and_hidden_scores():
+    """Scores that grow by far more than the lazy maximum's headroom from block to block, and a first key
+    block whose scores are all hugely negative: the running maximum has to move at the right blocks."""
+    import paper_2606_26997_amd as rp
+    print("[case] prefill large scores", flush=True)
+    w = make_prefill_workload(num_q_heads=4, num_kv_heads=2, head_dim=64, prefix_lens=[200, 130], seed=2)
+    q, k = (torch.from_numpy(x.view(np.int16).copy()).view(torch.bfloat16) for x in (w.q, w.k))
+    ramp = torch.ones(330)
+    ramp[:200] = torch.linspace(-40, 40, 200)
+    ramp[200:232] = -300.0
+    q = (q.abs() + 0.5).to(torch.bfloat16)
+    k = ((k.abs() * 0.05 + 1.0) * ramp.view(-1, 1, 1)).to(torch.bfloat16)
+    bits = lambda x: x.view(torch.int16).numpy().view(np.uint16)
+    w.q, w.k = bits(q), bits(k)
+    b = rp.PrefillBatch.from_workload(w)
+    b.prefill()
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle.prefill_attention(w.q, w.k, w.v, w.prefix_offs, w.softmax_scale)
+    out, lse = b.out.float().cpu().numpy().astype(np.float64), b.lse.cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(out - ref) <= 5e-3 * np.linalg.norm(ref)
+    # fp32 scores of magnitude up to 4000: an ulp is 2.4e-4, a dot product of 64 terms adds a few.
+    assert np.abs(lse - ref_lse).max() <= 4e-3
