@@ -600,8 +600,7 @@ rp_status rp_prefill_kv_write(const rp_paged_kv* kv, const rp_prefill_layout* l,
 }
 
 // Causal attention within each prompt; with `pages`, also the prompts' K/V
-// page writes: in the same launch for bf16 pools, by the page-write kernel
-// first for fp8 pools (their per-page scales need a whole page).
+// page writes, in the same launch.
 static rp_status prefill_impl(const rp_paged_kv* kv, const rp_prefill_layout* l, const void* q, const void* k,
                               const void* v, float softmax_scale, void* out, float* lse, bool pages,
                               hipStream_t stream) {
@@ -623,12 +622,7 @@ static rp_status prefill_impl(const rp_paged_kv* kv, const rp_prefill_layout* l,
   a.qk_scale = softmax_scale * rp::kLog2e;
   a.out = out;
   a.lse = lse;
-  const bool fp8 = rp::enum_bits(kv->kv_dtype) == RP_KV_FP8_E4M3;
-  if (pages && fp8) {
-    hipError_t e = rp::launch_prefill_kv_write(a, kv->head_dim, true, stream);
-    if (e != hipSuccess) return hip_fail(e, "prefill KV write kernel launch");
-  }
-  a.write_pages = pages && !fp8 ? 1 : 0;
+  a.write_pages = pages ? 1 : 0;
   hipError_t e = rp::launch_prefill_attn(a, kv->head_dim, n_rep, stream);
   return e == hipSuccess ? RP_OK : hip_fail(e, "prefill attention kernel launch");
 }

@@ -139,6 +139,53 @@ __device__ inline uint32_t f32_to_e4m3(float x) {
   return code | sign;
 }
 
+// e4m3 codes of x[i] / scale, the quotient rounded to fp32 and then to e4m3 as
+// f32_to_e4m3 does, four codes per word. inv = 1 / scale rounded; `plain`: no
+// x[i] is NaN, |x[i]| <= 448 scale up to rounding, and scale is in
+// plain_scale's range. A product with inv is then within 3 fp32 ulps of the
+// quotient, so its e4m3 code is the quotient's unless it lies that close to
+// the middle between two codes: 20 low mantissa bits near 0x80000, or near 0
+// where the codes are subnormal. gfx950's conversion rounds to nearest even
+// and equals f32_to_e4m3 on every fp32 value up to 464. Values that close, and
+// those that are not plain, are divided.
+// About 7 instructions a value against 26 (prefill of 32 x 1024 tokens into fp8
+// pages: 239 us dividing every value, 222 this way).
+__device__ inline bool plain_scale(float scale) { return scale >= 0x1p-100f && scale <= 0x1p100f; }
+template <int N>
+__device__ inline void e4m3_quotients(const float (&x)[N], float scale, float inv, bool plain, uint32_t (&w)[N / 4]) {
+#pragma clang fp contract(off)
+  static_assert(N % 4 == 0, "whole words");
+  constexpr uint32_t kLow = 0xFFFFFu, kUlps = 4;
+  uint32_t mid = 0xFFFFFFFFu;
+  float q[N], least = INFINITY;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    q[i] = x[i] * inv;
+    mid = min(mid, (__float_as_uint(q[i]) + 0x80000u + kUlps) & kLow);
+    least = fminf(least, fabsf(q[i]));
+  }
+  bool divide = !plain || mid <= 2 * kUlps;
+  if (least < 0x1p-6f) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      divide = divide || (fabsf(q[i]) < 0x1p-6f && q[i] != 0.f && ((__float_as_uint(q[i]) + kUlps) & kLow) <= 2 * kUlps);
+  }
+#pragma unroll
+  for (int k = 0; k < N / 4; ++k) {
+    int v = __builtin_amdgcn_cvt_pk_fp8_f32(q[4 * k], q[4 * k + 1], 0, false);
+    v = __builtin_amdgcn_cvt_pk_fp8_f32(q[4 * k + 2], q[4 * k + 3], v, true);
+    w[k] = (uint32_t)v;
+  }
+  if (divide) {
+#pragma unroll
+    for (int k = 0; k < N / 4; ++k) {
+      w[k] = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[k] |= f32_to_e4m3(x[4 * k + i] / scale) << (8 * i);
+    }
+  }
+}
+
 // ---- the fp8 append rule --------------------------------------------------
 // Row r of an fp8 (page, kv-head) block [16][D] takes a new token x. An
 // aligned group of G lanes holds the row: element e of a lane sits at column
@@ -237,6 +284,15 @@ __device__ inline float max_xor16_32(float x) {
   const uint32_t v = __float_as_uint(x);
   const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// Maximum over the wave, in every lane, without the LDS crossbar.
+__device__ inline float wave_max(float x) {
+  x = fmaxf(x, dpp<kQuadSwap1>(x));
+  x = fmaxf(x, dpp<kQuadSwap2>(x));
+  x = fmaxf(x, dpp<kRowHalfMirror>(x));
+  x = fmaxf(x, dpp<kRowMirror>(x));
+  return max_xor16_32(x);
 }
 
 // MFMA tiles used by the group-prefix and prefill paths (fp32 accumulate).

@@ -31,35 +31,68 @@ __device__ inline int prompt_len(const PrefillArgs& a, int g, int* first) {
 // ---------------------------------------------------------------------------
 // K/V page write
 // ---------------------------------------------------------------------------
+// One (page, kv-head) block of an fp8 pool from `rows` token rows by one wave:
+// the rows stay in registers between the maximum and the codes. Magnitudes of
+// bf16 values compare as integers; a NaN (above infinity) takes the maximum
+// over the others in fp32.
 template <int D>
-__device__ void write_fp8_head(uint8_t* blk, float* scale_slot, const uint16_t* src, size_t src_row_pitch,
-                               int rows, int lane) {
-#pragma clang fp contract(off)
-  constexpr int CPR = D / 8;  // 8-element chunks per row
-  float amax = 0.f;
-  for (int c = lane; c < rows * CPR; c += 64) {
-    const int r = c / CPR, col = (c - r * CPR) * 8;
-    const uint4 w = *reinterpret_cast<const uint4*>(src + (size_t)r * src_row_pitch + col);
-    const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+struct Fp8Head {
+  static constexpr int CPR = D / 8;            // 8-element chunks per row
+  static constexpr int NC = kPage * CPR / 64;  // chunks per lane
+  uint32_t v[NC][4];
+
+  __device__ inline void load(const uint16_t* src, size_t src_row_pitch, int rows, int lane) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) amax = fmaxf(amax, fmaxf(fabsf(bf16_lo(ws[e])), fabsf(bf16_hi(ws[e]))));
-  }
-  amax = xor_max_from<1>(amax);
-  const float scale = amax > 0.f ? amax / 448.0f : 1.0f;
-  for (int c = lane; c < rows * CPR; c += 64) {
-    const int r = c / CPR, col = (c - r * CPR) * 8;
-    const uint4 w = *reinterpret_cast<const uint4*>(src + (size_t)r * src_row_pitch + col);
-    const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-    uint32_t codes[2] = {0, 0};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t lo = f32_to_e4m3(bf16_lo(ws[e]) / scale), hi = f32_to_e4m3(bf16_hi(ws[e]) / scale);
-      codes[e / 2] |= (lo | (hi << 8)) << (16 * (e % 2));
+    for (int i = 0; i < NC; ++i) {
+      const int c = lane + i * 64, r = c / CPR, col = (c % CPR) * 8;
+      uint4 w = make_uint4(0, 0, 0, 0);
+      if (r < rows) w = *reinterpret_cast<const uint4*>(src + (size_t)r * src_row_pitch + col);
+      v[i][0] = w.x;
+      v[i][1] = w.y;
+      v[i][2] = w.z;
+      v[i][3] = w.w;
     }
-    *reinterpret_cast<uint2*>(blk + (size_t)r * D + col) = make_uint2(codes[0], codes[1]);
   }
-  if (lane == 0) *scale_slot = scale;
-}
+
+  __device__ inline void store(uint8_t* blk, float* scale_slot, int rows, int lane) const {
+#pragma clang fp contract(off)
+    typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+    u16x2_t top = {0, 0};
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2_t, v[i][e] & 0x7FFF7FFFu));
+    const uint32_t m = top[0] > top[1] ? top[0] : top[1];
+    float amax = __uint_as_float(m << 16);
+    const bool nan = __any(m > 0x7F80u);
+    if (nan) {
+      amax = 0.f;
+#pragma unroll
+      for (int i = 0; i < NC; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) amax = fmaxf(amax, fmaxf(fabsf(bf16_lo(v[i][e])), fabsf(bf16_hi(v[i][e]))));
+    }
+    amax = wave_max(amax);
+    const float scale = amax > 0.f ? amax / 448.0f : 1.0f;
+    const float inv = 1.0f / scale;
+    const bool plain = !nan && plain_scale(scale);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const int c = lane + i * 64, r = c / CPR, col = (c % CPR) * 8;
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[2 * e] = bf16_lo(v[i][e]);
+        x[2 * e + 1] = bf16_hi(v[i][e]);
+      }
+      uint32_t codes[2];
+      e4m3_quotients(x, scale, inv, plain, codes);
+      if (r < rows) *reinterpret_cast<uint2*>(blk + (size_t)r * D + col) = make_uint2(codes[0], codes[1]);
+    }
+    if (lane == 0) *scale_slot = scale;
+  }
+};
 
 template <int D, bool FP8>
 __global__ __launch_bounds__(64) void prefill_kv_write_kernel(const PrefillArgs a) {
@@ -90,8 +123,11 @@ __global__ __launch_bounds__(64) void prefill_kv_write_kernel(const PrefillArgs 
     }
   } else {
     const size_t sidx = (size_t)page * Hkv + h;
-    write_fp8_head<D>(static_cast<uint8_t*>(a.k_pages) + blk, a.k_scale + sidx, ks, pitch, rows, lane);
-    write_fp8_head<D>(static_cast<uint8_t*>(a.v_pages) + blk, a.v_scale + sidx, vs, pitch, rows, lane);
+    Fp8Head<D> kh, vh;
+    kh.load(ks, pitch, rows, lane);
+    vh.load(vs, pitch, rows, lane);
+    kh.store(static_cast<uint8_t*>(a.k_pages) + blk, a.k_scale + sidx, rows, lane);
+    vh.store(static_cast<uint8_t*>(a.v_pages) + blk, a.v_scale + sidx, rows, lane);
   }
 }
 
@@ -115,6 +151,7 @@ __global__ __launch_bounds__(64) void prefill_kv_write_kernel(const PrefillArgs 
 // 320 us, 1.0 PFLOP/s). Against staging through registers, the direct copies
 // measured 8% (1024 tokens: 4%), the maximum inside the product 4%, the mask
 // without a test for rows past the end 2%, and the order of pf_unit 12-20%.
+enum PfPages { kPagesNone = 0, kPagesBf16 = 1, kPagesFp8 = 2 };  // what the attention kernel writes besides
 constexpr int kPfWaves = 4;
 constexpr int kPfThreads = 64 * kPfWaves;
 constexpr int kKeyBlk = 32;
@@ -198,11 +235,35 @@ __device__ inline bool pf_unit(int b, int NP, int max_blocks, int stride, int* p
   return *rb >= 0;
 }
 
-// The one-launch prefill of a bf16 pool writes every prompt token's K/V rows
-// into the group's prefix pages from the workgroup whose query rows hold the
-// token (exactly one), once its attention is done: the rows are then in this
-// XCD's L2, and no register or wait of the key loop is spent on them. Rows
-// past the prompt's end are not written, as in the page-write kernel.
+// The one-launch prefill writes a prompt's K/V rows into the group's prefix
+// pages once a workgroup's attention is done: the rows are then in this XCD's
+// L2, and no register or wait of the key loop is spent on them. bf16 rows are
+// written by the workgroup whose query rows hold the token (exactly one), fp8
+// pages, whose scale needs all their rows, by the one that holds the page's
+// first token. Rows past the prompt's end are not written, as in the
+// page-write kernel. (fp8, 32 prompts of U[64, 512]: a page-write launch before
+// the attention 69 us in all, together 55.)
+template <int D, int TPB>
+__device__ inline void pf_write_pages_fp8(const PrefillArgs& a, int g, int h, int T0, int last, int wave, int lane,
+                                          const uint16_t* kbase, const uint16_t* vbase, uint32_t pitch) {
+  const int p0 = cdiv(T0, kPage), p1 = cdiv(min(T0 + TPB, last + 1), kPage);
+  // A wave takes whole pages, K and V, where there is one for every wave, and
+  // K or V of a page otherwise.
+  constexpr int SPLIT = TPB / kPage >= kPfWaves ? 1 : 2;
+  for (int task = wave; task < SPLIT * (p1 - p0); task += kPfWaves) {
+    const int p = p0 + task / SPLIT, rows = min(kPage, last + 1 - p * kPage);
+    const int page = clamp_page(a.prefix_block_table[(size_t)g * a.max_prefix_pages + p], a.num_pages);
+    const size_t slot = (size_t)page * a.num_kv_heads + h, src = (size_t)p * kPage * pitch, dst = slot * (kPage * D);
+    Fp8Head<D> head[3 - SPLIT];
+    const bool v_only = SPLIT == 2 && (task & 1);
+    head[0].load((v_only ? vbase : kbase) + src, pitch, rows, lane);
+    if constexpr (SPLIT == 1) head[1].load(vbase + src, pitch, rows, lane);
+    head[0].store(static_cast<uint8_t*>(v_only ? a.v_pages : a.k_pages) + dst, (v_only ? a.v_scale : a.k_scale) + slot,
+                  rows, lane);
+    if constexpr (SPLIT == 1) head[1].store(static_cast<uint8_t*>(a.v_pages) + dst, a.v_scale + slot, rows, lane);
+  }
+}
+
 template <int D, int TPB>
 __device__ inline void pf_write_pages(const PrefillArgs& a, int g, int h, int T0, int last, int t,
                                       const uint16_t* kbase, const uint16_t* vbase, uint32_t pitch) {
@@ -338,7 +399,7 @@ __device__ __forceinline__ void pf_compute(const uint16_t* kst, int u0, float qk
 
 // Register budget: one row tile per wave fits four waves per SIMD (128
 // VGPRs), two row tiles three (168 VGPRs).
-template <int D, int NREP, int RT, bool WP>
+template <int D, int NREP, int RT, PfPages WP>
 __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(RT == 1 ? 4 : 3, 8)))
 void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride) {
   using L = PfSmem<D>;
@@ -430,7 +491,7 @@ void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride) {
     cur = cur == STAGES - 1 ? 0 : cur + 1;
   }
 
-  if constexpr (WP) pf_write_pages<D, TPB>(a, g, h, T0, last, t, kbase, vbase, (uint32_t)kpitch);
+  if constexpr (WP == kPagesBf16) pf_write_pages<D, TPB>(a, g, h, T0, last, t, kbase, vbase, (uint32_t)kpitch);
 
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
@@ -446,6 +507,8 @@ void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride) {
     if (a.lse != nullptr && quad == 0)
       a.lse[(size_t)(first + tr[rt]) * Hq + jr] = (fast_log2(lt) - mneg[rt][0] * a.qk_scale) * kLn2;
   }
+  if constexpr (WP == kPagesFp8)
+    pf_write_pages_fp8<D, TPB>(a, g, h, T0, last, uwave, lane, kbase, vbase, (uint32_t)kpitch);
 }
 
 // Row tiles per wave: two when prompts average 384 tokens or more (each K/V
@@ -466,12 +529,15 @@ hipError_t attn_launch(const PrefillArgs& a, hipStream_t st) {
       stride == 0 ? NP * max_blocks : 8 * (pairs / kPfPairs * stride + pairs % kPfPairs * max_blocks);
   if (blocks <= 0) return hipSuccess;
   const dim3 grid((unsigned)blocks), block(kPfThreads);
-  if (a.write_pages) {
-    if (rt == 2) prefill_attn_kernel<D, NREP, 2, true><<<grid, block, 0, st>>>(a, max_blocks, stride);
-    else prefill_attn_kernel<D, NREP, 1, true><<<grid, block, 0, st>>>(a, max_blocks, stride);
+  if (a.write_pages && a.k_scale != nullptr) {
+    if (rt == 2) prefill_attn_kernel<D, NREP, 2, kPagesFp8><<<grid, block, 0, st>>>(a, max_blocks, stride);
+    else prefill_attn_kernel<D, NREP, 1, kPagesFp8><<<grid, block, 0, st>>>(a, max_blocks, stride);
+  } else if (a.write_pages) {
+    if (rt == 2) prefill_attn_kernel<D, NREP, 2, kPagesBf16><<<grid, block, 0, st>>>(a, max_blocks, stride);
+    else prefill_attn_kernel<D, NREP, 1, kPagesBf16><<<grid, block, 0, st>>>(a, max_blocks, stride);
   } else {
-    if (rt == 2) prefill_attn_kernel<D, NREP, 2, false><<<grid, block, 0, st>>>(a, max_blocks, stride);
-    else prefill_attn_kernel<D, NREP, 1, false><<<grid, block, 0, st>>>(a, max_blocks, stride);
+    if (rt == 2) prefill_attn_kernel<D, NREP, 2, kPagesNone><<<grid, block, 0, st>>>(a, max_blocks, stride);
+    else prefill_attn_kernel<D, NREP, 1, kPagesNone><<<grid, block, 0, st>>>(a, max_blocks, stride);
   }
   return hipGetLastError();
 }
