@@ -1,7 +1,8 @@
-// KV append: one wave per (sequence, kv-head) writes the new token into
-// response slot L = resp_lens[s] (page resp_block_table[s][L / 16], row L % 16).
-// bf16 pools copy the values; fp8 pools apply the per-(page, kv-head) scale
-// rule of append_fp8_row. Lane l handles columns l + 64 e.
+// KV append: the new token of sequence s goes into response slot L =
+// resp_lens[s] (page resp_block_table[s][L / 16], row L % 16). bf16 pools copy
+// the values, 16 bytes per thread; fp8 pools apply the per-(page, kv-head)
+// scale rule of append_fp8_row, D / 4 lanes per row, K and V of a kv-head side
+// by side in one wave.
 #include "rp_device.h"
 #include "rp_internal.h"
 
@@ -10,41 +11,44 @@
 namespace rp {
 namespace {
 
-template <int D, bool FP8>
-__global__ __launch_bounds__(64) void append_kernel(const AppendArgs a) {
-  constexpr int EPL = D / 64;
-  const int Hkv = a.num_kv_heads;
-  const int s = blockIdx.x / Hkv;
-  const int h = blockIdx.x - s * Hkv;
+constexpr int kAppendThreads = 256;
+
+template <int D>
+__global__ __launch_bounds__(kAppendThreads) void append_bf16_kernel(const AppendArgs a) {
+  constexpr int CPR = D / 8;  // 16-byte pieces per row
+  const int per_seq = 2 * a.num_kv_heads * CPR;
+  const long long i = (long long)blockIdx.x * kAppendThreads + threadIdx.x;
+  const int s = (int)(i / per_seq);
+  if (s >= a.num_seqs) return;
+  const int c = (int)(i - (long long)s * per_seq);
+  const int h = c / (2 * CPR), v = c / CPR % 2, col = c % CPR * 8;
   const int L = a.resp_lens[s];
+  const uint16_t* src = static_cast<const uint16_t*>(v ? a.v_new : a.k_new);
+  const uint4 w = *reinterpret_cast<const uint4*>(src + ((size_t)s * a.num_kv_heads + h) * D + col);
   if (L < 0 || L >= a.max_resp_pages * kPage) return;  // no slot for the new token
   const int page = clamp_page(a.resp_block_table[(size_t)s * a.max_resp_pages + L / kPage], a.num_pages);
-  const int r = L % kPage;
-  const int lane = threadIdx.x;
-  const size_t head_off = ((size_t)s * Hkv + h) * D;
-  const uint16_t* kn = static_cast<const uint16_t*>(a.k_new) + head_off;
-  const uint16_t* vn = static_cast<const uint16_t*>(a.v_new) + head_off;
-  const size_t blk = ((size_t)page * Hkv + h) * kPage * D;  // in elements
-  if constexpr (!FP8) {
-    uint16_t* kd = static_cast<uint16_t*>(a.k_pages) + blk + (size_t)r * D + lane;
-    uint16_t* vd = static_cast<uint16_t*>(a.v_pages) + blk + (size_t)r * D + lane;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      kd[64 * e] = kn[64 * e + lane];
-      vd[64 * e] = vn[64 * e + lane];
-    }
-  } else {
-    const size_t sidx = (size_t)page * Hkv + h;
-    float kx[EPL], vx[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      kx[e] = __uint_as_float((uint32_t)kn[64 * e + lane] << 16);
-      vx[e] = __uint_as_float((uint32_t)vn[64 * e + lane] << 16);
-    }
-    const auto col = [lane](int e) { return lane + 64 * e; };
-    append_fp8_row<D, 64>(static_cast<uint8_t*>(a.k_pages) + blk, a.k_scale + sidx, r, kx, col, lane == 0);
-    append_fp8_row<D, 64>(static_cast<uint8_t*>(a.v_pages) + blk, a.v_scale + sidx, r, vx, col, lane == 0);
-  }
+  uint16_t* dst = static_cast<uint16_t*>(v ? a.v_pages : a.k_pages);
+  *reinterpret_cast<uint4*>(dst + (((size_t)page * a.num_kv_heads + h) * kPage + L % kPage) * D + col) = w;
+}
+
+template <int D>
+__global__ __launch_bounds__(64) void append_fp8_kernel(const AppendArgs a) {
+  constexpr int G = D / 4;  // lanes per row
+  const int Hkv = a.num_kv_heads;
+  const int s = blockIdx.x / Hkv, h = blockIdx.x - s * Hkv;
+  const int L = a.resp_lens[s];
+  if (L < 0 || L >= a.max_resp_pages * kPage) return;  // no slot for the new token
+  const int lane = threadIdx.x, v = lane / G, l = lane % G;
+  if (v > 1) return;
+  const uint16_t* src = static_cast<const uint16_t*>(v ? a.v_new : a.k_new) + ((size_t)s * Hkv + h) * D;
+  const uint2 w = *reinterpret_cast<const uint2*>(src + l * 4);
+  const int page = clamp_page(a.resp_block_table[(size_t)s * a.max_resp_pages + L / kPage], a.num_pages);
+  const size_t slot = (size_t)page * Hkv + h;
+  float* scale = (v ? a.v_scale : a.k_scale) + slot;
+  const float x[4] = {bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y)};
+  const int col[1] = {l * 4};
+  append_fp8_row<D, G, 4>(static_cast<uint8_t*>(v ? a.v_pages : a.k_pages) + slot * (kPage * D), scale, *scale,
+                          L % kPage, x, col, l == 0);
 }
 
 // Layout checker (test utility): records the number of bad entries and one example.
@@ -88,17 +92,17 @@ __global__ __launch_bounds__(256) void validate_kernel(const ValidateArgs a) {
 }  // namespace
 
 hipError_t launch_append(const AppendArgs& a, int head_dim, bool fp8, hipStream_t stream) {
-  const long long blocks = (long long)a.num_seqs * a.num_kv_heads;
-  if (blocks <= 0) return hipSuccess;
-  const dim3 grid((unsigned)blocks), block(64);
-  if (head_dim == 128) {
-    if (fp8) append_kernel<128, true><<<grid, block, 0, stream>>>(a);
-    else append_kernel<128, false><<<grid, block, 0, stream>>>(a);
-  } else if (head_dim == 64) {
-    if (fp8) append_kernel<64, true><<<grid, block, 0, stream>>>(a);
-    else append_kernel<64, false><<<grid, block, 0, stream>>>(a);
+  const long long rows = (long long)a.num_seqs * a.num_kv_heads;
+  if (rows <= 0) return hipSuccess;
+  if (head_dim != 128 && head_dim != 64) return hipErrorInvalidValue;
+  if (fp8) {
+    const dim3 grid((unsigned)rows), block(64);
+    if (head_dim == 128) append_fp8_kernel<128><<<grid, block, 0, stream>>>(a);
+    else append_fp8_kernel<64><<<grid, block, 0, stream>>>(a);
   } else {
-    return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((rows * 2 * (head_dim / 8) + kAppendThreads - 1) / kAppendThreads)), block(kAppendThreads);
+    if (head_dim == 128) append_bf16_kernel<128><<<grid, block, 0, stream>>>(a);
+    else append_bf16_kernel<64><<<grid, block, 0, stream>>>(a);
   }
   return hipGetLastError();
 }

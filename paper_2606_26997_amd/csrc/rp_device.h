@@ -186,56 +186,6 @@ __device__ inline void e4m3_quotients(const float (&x)[N], float scale, float in
   }
 }
 
-// ---- the fp8 append rule --------------------------------------------------
-// Row r of an fp8 (page, kv-head) block [16][D] takes a new token x. An
-// aligned group of G lanes holds the row: element e of a lane sits at column
-// col(e) (fp32 values of bf16 inputs); `leader` marks the one lane that
-// stores the scale. amax = max |x| over the row; row 0 sets
-// scale = amax / 448 (1 when amax is 0); a later row keeps the old scale when
-// amax <= 448 * old, and otherwise sets scale = amax / 448 after requantising
-// rows 0..r-1 from code * old. Plain IEEE fp32 (no contraction, correctly
-// rounded division), so the bytes are a deterministic function of the inputs.
-// Every lane of a G-lane group must call it, with the same r.
-template <int D, int G, int N, class ColFn>
-__device__ void append_fp8_row(uint8_t* blk, float* scale_slot, int r, const float (&x)[N], ColFn col,
-                               bool leader) {
-#pragma clang fp contract(off)
-  float amax = 0.f;
-#pragma unroll
-  for (int e = 0; e < N; ++e) amax = fmaxf(amax, fabsf(x[e]));
-#pragma unroll
-  for (int o = 1; o < G; o <<= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
-  const float old = *scale_slot;
-  float scale;
-  if (r == 0) {
-    scale = amax > 0.f ? amax / 448.0f : 1.0f;
-  } else if (amax <= 448.0f * old) {
-    scale = old;
-  } else {
-    scale = amax / 448.0f;
-    // Requantise rows 0..r-1, four rows' codes in flight per memory round trip.
-    constexpr int kRows = 4;
-    for (int r0 = 0; r0 < r; r0 += kRows) {
-      uint32_t c[kRows][N];
-#pragma unroll
-      for (int k = 0; k < kRows; ++k)
-#pragma unroll
-        for (int e = 0; e < N; ++e) c[k][e] = r0 + k < r ? blk[(size_t)(r0 + k) * D + col(e)] : 0u;
-#pragma unroll
-      for (int k = 0; k < kRows; ++k) {
-        if (r0 + k >= r) break;
-        uint8_t* row = blk + (size_t)(r0 + k) * D;
-#pragma unroll
-        for (int e = 0; e < N; ++e) row[col(e)] = (uint8_t)f32_to_e4m3(e4m3_to_f32(c[k][e]) * old / scale);
-      }
-    }
-  }
-  uint8_t* row = blk + (size_t)r * D;
-#pragma unroll
-  for (int e = 0; e < N; ++e) row[col(e)] = (uint8_t)f32_to_e4m3(x[e] / scale);
-  if (leader) *scale_slot = scale;
-}
-
 // ---- wavefront reductions -----------------------------------------------
 template <int CTRL>
 __device__ inline float dpp(float x) {
@@ -286,13 +236,110 @@ __device__ inline float max_xor16_32(float x) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// Maximum over the wave, in every lane, without the LDS crossbar.
-__device__ inline float wave_max(float x) {
+// Maxima over aligned groups of 16 lanes, over lanes l and l^16, and over the
+// wave, in every lane, without the LDS crossbar.
+__device__ inline float group_max16(float x) {
   x = fmaxf(x, dpp<kQuadSwap1>(x));
   x = fmaxf(x, dpp<kQuadSwap2>(x));
   x = fmaxf(x, dpp<kRowHalfMirror>(x));
-  x = fmaxf(x, dpp<kRowMirror>(x));
-  return max_xor16_32(x);
+  return fmaxf(x, dpp<kRowMirror>(x));
+}
+__device__ inline float max_xor16(float x) {
+  const uint32_t v = __float_as_uint(x);
+  const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ inline float wave_max(float x) { return max_xor16_32(group_max16(x)); }
+
+// ---- the fp8 append rule --------------------------------------------------
+// Row r of an fp8 (page, kv-head) block [16][D] takes a new token x. An
+// aligned group of G lanes holds the row, N fp32 values (of bf16 inputs) a
+// lane, in N / CH runs of CH consecutive columns: run k starts at col[k].
+// `old` is the block's scale (its value does not matter for r = 0); `leader`
+// marks the one lane that stores the new one. amax = max |x| over the row; row
+// 0 sets scale = amax / 448 (1 when amax is 0); a later row keeps the old
+// scale when amax <= 448 * old, and otherwise sets scale = amax / 448 after
+// requantising rows 0..r-1 from code * old. Plain IEEE fp32 (no contraction,
+// quotients as the division rounds them), so the bytes are a deterministic
+// function of the inputs. Every lane of a G-lane group must call it, with the
+// same r.
+//
+// The rule is a chain of memory round trips, so callers load `old` early, and
+// the requantised rows come in whole words, eight rows per round trip (one
+// byte a load, the page and its scale loaded after the rotation: 1024
+// sequences' prep into fp8 pages 24.4 us; this way 13.4).
+template <int CH, int N>
+__device__ inline void put_codes(uint8_t* row, const int (&col)[N / CH], const uint32_t (&w)[N / 4]) {
+#pragma unroll
+  for (int k = 0; k < N / CH; ++k) {
+    if constexpr (CH == 4) *reinterpret_cast<uint32_t*>(row + col[k]) = w[k];
+    else *reinterpret_cast<uint16_t*>(row + col[k]) = (uint16_t)(w[k / 2] >> (16 * (k % 2)));
+  }
+}
+template <int CH, int N>
+__device__ inline void get_codes(const uint8_t* row, const int (&col)[N / CH], uint32_t (&w)[N / 4]) {
+#pragma unroll
+  for (int k = 0; k < N / CH; ++k) {
+    if constexpr (CH == 4) w[k] = *reinterpret_cast<const uint32_t*>(row + col[k]);
+    else if (k % 2 == 0) w[k / 2] = *reinterpret_cast<const uint16_t*>(row + col[k]);
+    else w[k / 2] |= (uint32_t)*reinterpret_cast<const uint16_t*>(row + col[k]) << 16;
+  }
+}
+template <int D, int G, int CH, int N>
+__device__ void append_fp8_row(uint8_t* blk, float* scale_slot, float old, int r, const float (&x)[N],
+                               const int (&col)[N / CH], bool leader) {
+#pragma clang fp contract(off)
+  static_assert(G == 16 || G == 32, "lanes per row");
+  static_assert(CH == 4 || (CH == 2 && N % 4 == 0), "columns per run");
+  float amax = 0.f;
+  bool plain = true;  // no NaN element
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    amax = fmaxf(amax, fabsf(x[e]));
+    plain = plain && x[e] == x[e];
+  }
+  amax = group_max16(amax);
+  if constexpr (G == 32) amax = max_xor16(amax);
+  float scale;
+  if (r == 0) {
+    scale = amax > 0.f ? amax / 448.0f : 1.0f;
+  } else if (amax <= 448.0f * old) {
+    scale = old;
+  } else {
+    scale = amax / 448.0f;
+    const float inv = 1.0f / scale;
+    const bool scales = plain_scale(scale) && plain_scale(old);
+    constexpr int kRows = 8;
+    for (int r0 = 0; r0 < r; r0 += kRows) {
+      uint32_t c[kRows][N / 4];
+#pragma unroll
+      for (int k = 0; k < kRows; ++k)
+        if (r0 + k < r) get_codes<CH, N>(blk + (size_t)(r0 + k) * D, col, c[k]);
+#pragma unroll
+      for (int k = 0; k < kRows; ++k) {
+        if (r0 + k >= r) break;
+        float y[N];
+        uint32_t nan = 0;  // bytes with the NaN code carry into their top bit
+#pragma unroll
+        for (int i = 0; i < N / 4; ++i) {
+          nan |= (c[k][i] & 0x7F7F7F7Fu) + 0x01010101u;
+          const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)c[k][i], false);
+          const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)c[k][i], true);
+          y[4 * i] = lo[0] * old;
+          y[4 * i + 1] = lo[1] * old;
+          y[4 * i + 2] = hi[0] * old;
+          y[4 * i + 3] = hi[1] * old;
+        }
+        uint32_t w[N / 4];
+        e4m3_quotients(y, scale, inv, scales && (nan & 0x80808080u) == 0, w);
+        put_codes<CH, N>(blk + (size_t)(r0 + k) * D, col, w);
+      }
+    }
+  }
+  uint32_t w[N / 4];
+  e4m3_quotients(x, scale, 1.0f / scale, plain && plain_scale(scale), w);
+  put_codes<CH, N>(blk + (size_t)r * D, col, w);
+  if (leader) *scale_slot = scale;
 }
 
 // MFMA tiles used by the group-prefix and prefill paths (fp32 accumulate).

@@ -69,8 +69,16 @@ __device__ inline double bf16_word_f64(const uint32_t* w, int p) {
   return (double)(p & 1 ? bf16_hi(w[p >> 1]) : bf16_lo(w[p >> 1]));
 }
 
+// Where the sequence's new token goes: first (page, kv-head) block of its page
+// (-1: nowhere) and row in it.
+struct AppendAt {
+  long long slot;
+  int row;
+};
+
 template <int D, bool FP8>
-__device__ inline void prep_slot(const QkPrepArgs& a, int s, int kind, int head, int l16, int L,
+__device__ inline void prep_slot(const QkPrepArgs& a, int s, int kind, int head, int l16, const AppendAt& at,
+                                 float old_scale,
                                  const uint32_t (&x1)[D / 64], const uint32_t (&x2)[D / 64],
                                  const double (*s_tab)[4][D / 2]) {
   constexpr int NP = D / 32;   // pairs per lane
@@ -142,12 +150,10 @@ __device__ inline void prep_slot(const QkPrepArgs& a, int s, int kind, int head,
   }
 
   // Append of k (kind 1) or v (kind 2) at response slot L.
-  if (L < 0 || L >= a.max_resp_pages * kPage) return;  // no slot for the new token
-  const int page = clamp_page(a.resp_block_table[(size_t)s * a.max_resp_pages + L / kPage], a.num_pages);
-  const int r = L % kPage;
-  const size_t blk = ((size_t)page * Hkv + head) * kPage * D;  // in elements
+  if (at.slot < 0) return;  // no slot for the new token
+  const size_t blk = ((size_t)at.slot + head) * kPage * D;  // in elements
   if constexpr (!FP8) {
-    uint16_t* dst = static_cast<uint16_t*>(kind == 1 ? a.k_pages : a.v_pages) + blk + (size_t)r * D;
+    uint16_t* dst = static_cast<uint16_t*>(kind == 1 ? a.k_pages : a.v_pages) + blk + (size_t)at.row * D;
     store_words<W>(dst, c1, o1);
     store_words<W>(dst, c2, o2);
   } else {
@@ -157,10 +163,10 @@ __device__ inline void prep_slot(const QkPrepArgs& a, int s, int kind, int head,
       xf[p] = p & 1 ? bf16_hi(o1[p >> 1]) : bf16_lo(o1[p >> 1]);
       xf[NP + p] = p & 1 ? bf16_hi(o2[p >> 1]) : bf16_lo(o2[p >> 1]);
     }
-    const auto col = [c1, c2](int e) { return e < NP ? c1 + e : c2 + (e - NP); };
-    uint8_t* pages = static_cast<uint8_t*>(kind == 1 ? a.k_pages : a.v_pages);
-    float* scales = kind == 1 ? a.k_scale : a.v_scale;
-    append_fp8_row<D, kSlotLanes>(pages + blk, scales + (size_t)page * Hkv + head, r, xf, col, l16 == 0);
+    const int col[2] = {c1, c2};
+    append_fp8_row<D, kSlotLanes, NP>(static_cast<uint8_t*>(kind == 1 ? a.k_pages : a.v_pages) + blk,
+                                      (kind == 1 ? a.k_scale : a.v_scale) + at.slot + head, old_scale, at.row, xf, col,
+                                      l16 == 0);
   }
 }
 
@@ -199,6 +205,20 @@ __device__ __forceinline__ void prep_block(const QkPrepArgs& a, int bid, PrepTab
       load_words<W>(src, c2, x2[k]);
     }
   }
+  // The append's page, and the scales it starts from, are loaded here too, so
+  // that their round trips pass behind the tables.
+  AppendAt at = {-1, 0};
+  float old_scale[SPL];
+  if (L >= 0 && L < a.max_resp_pages * kPage) {
+    at.slot = (long long)clamp_page(a.resp_block_table[(size_t)s * a.max_resp_pages + L / kPage], a.num_pages) * Hkv;
+    at.row = L % kPage;
+  }
+#pragma unroll
+  for (int k = 0; k < SPL; ++k) {
+    old_scale[k] = 1.f;
+    if (FP8 && at.slot >= 0 && (kind[k] == 1 || kind[k] == 2))
+      old_scale[k] = (kind[k] == 1 ? a.k_scale : a.v_scale)[at.slot + head[k]];
+  }
   if (t < HALF) {
     const double pos = (double)a.prefix_lens[g] + (double)L;
     double sn, cs;
@@ -217,7 +237,7 @@ __device__ __forceinline__ void prep_block(const QkPrepArgs& a, int bid, PrepTab
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < SPL; ++k) {
-    if (kind[k] < 3) prep_slot<D, FP8>(a, s, kind[k], head[k], l16, L, x1[k], x2[k], s_tab);
+    if (kind[k] < 3) prep_slot<D, FP8>(a, s, kind[k], head[k], l16, at, old_scale[k], x1[k], x2[k], s_tab);
   }
 }
 
