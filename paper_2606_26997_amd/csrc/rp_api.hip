@@ -201,6 +201,27 @@ rp::PlanView plan_view(void* ws, const WsLayout& w) {
   return v;
 }
 
+// Whether rp_group_decode_attn runs as one launch, a workgroup per (sequence,
+// kv-head), instead of plan, parts and combine. Its seven shares of a
+// sequence's pages (as many as the tables hold) take steps of 8 KiB of K and V
+// one after the other, about 0.85 us each, where the three launches take 13-18
+// us however short the batch; with four or more query rows per kv-head those
+// take longer (a group's rows need several passes over its prefix). Measured,
+// three launches against one, in us (Hq / Hkv, sequences x kv-heads x pages):
+//   2: 4 x 2 x 12 13.2, 8.2; 16 x 8 x 64 19.3, 15.0; 16 x 8 x 126 21.1, 24.8;
+//      2 x 8 x 128 18.1, 20.7; 64 x 8 x 32 22.6, 16.3
+//   4: 16 x 2 x 126 27.9, 23.9;  8: 64 x 2 x 63 49.8, 16.3; 8 x 4 x 129 44.0, 24.0
+// so the line lies at 10 and 20 steps. It reads a group's prefix once per
+// member, so the batch's tables may span at most 128 MiB of K and V; the plan
+// that it leaves in the workspace is made by one wave (at most 64 sequences).
+bool small_batch(const Shape& sh) {
+  const long long page_bytes = 2ll * rp::kPage * sh.D * (sh.fp8 ? 1 : 2);  // K and V of a (page, kv-head)
+  const long long pages = (long long)sh.max_pp + sh.max_rp, step_pages = 8192 / page_bytes;
+  const int steps = sh.nrep >= 4 ? 20 : 10;
+  return sh.S <= rp::kSmallPlanMaxSeqs && pages <= (rp::kSmallWaves - 1) * steps * step_pages &&
+         pages * sh.S * sh.Hkv * page_bytes <= (128ll << 20);
+}
+
 rp_status prepare(const rp_paged_kv* kv, const rp_group_layout* l, void* ws, size_t ws_bytes, Shape* sh,
                   WsLayout* w) {
   rp_status st = check_shape(kv, l, sh);
@@ -397,6 +418,14 @@ rp_status rp_group_decode_attn(const rp_paged_kv* kv, const rp_group_layout* l, 
   if (q == nullptr || !aligned(q, 16)) return fail(RP_ERR_INVALID_ARG, "q must be non-NULL and 16-byte aligned");
   if (out == nullptr || !aligned(out, 16)) return fail(RP_ERR_INVALID_ARG, "out must be non-NULL and 16-byte aligned");
   if (lse != nullptr && !aligned(lse, 4)) return fail(RP_ERR_INVALID_ARG, "lse must be 4-byte aligned");
+  if (small_batch(sh)) {
+    rp::PlanArgs p;
+    st = plan_args(sh, l, ws, w, 0, &p);
+    if (st != RP_OK) return st;
+    const rp::AttnArgs a = attn_args(kv, l, q, softmax_scale, p.view);
+    hipError_t e = rp::launch_attn_small(a, p, sh.D, sh.nrep, sh.fp8, out, lse, stream);
+    return e == hipSuccess ? RP_OK : hip_fail(e, "small attention kernel launch");
+  }
   st = rp_plan(kv, l, ws, ws_bytes, stream);
   if (st != RP_OK) return st;
   st = rp_attn_parts(kv, l, q, softmax_scale, ws, ws_bytes, stream);

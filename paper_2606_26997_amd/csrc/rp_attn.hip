@@ -36,6 +36,7 @@
 
 #include "rp_device.h"
 #include "rp_internal.h"
+#include "rp_plan_small.h"
 
 namespace rp {
 namespace {
@@ -126,10 +127,10 @@ __device__ inline void stage_v(const u32x4_t (&v)[Geom<D, FP8>::LOADS], int nval
 // COPIES = 2, lo takes a second product on hi's column if `third`; an infinite
 // v then makes the column NaN (0 times infinity), and the result false: the
 // caller runs the pages again without it. The lanes of term 0 write the row's
-// partial `part`.
+// partial to part_o [D] and part_lse.
 template <int D, bool FP8, int COPIES>
 __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int* bt, int npages, int ntok,
-                                             const uint16_t* qrow, int term, int part, uint16_t* vt,
+                                             const uint16_t* qrow, int term, float* part_o, float* part_lse, uint16_t* vt,
                                              bool third = true) {
   using G = Geom<D, FP8>;
   constexpr int EPL = G::EPL, LOADS = G::LOADS, PAGES = G::PAGES, DT = D / 16, PITCH = G::PITCH;
@@ -354,7 +355,7 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
   const float lt = xor_sum_from<16>(lrow);
   const float inv = 1.f / lt;
   const bool store = qrow != nullptr && term == 0;
-  float* dst = a.view.part_o + (size_t)part * D + quad * 4;
+  float* dst = part_o + quad * 4;
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
     float v[4];
@@ -370,7 +371,7 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
     }
     if (store) *reinterpret_cast<float4*>(dst + dt * 16) = make_float4(v[0], v[1], v[2], v[3]);
   }
-  if (store && quad == 0) a.view.part_lse[part] = (mrow + fast_log2(lt)) * kLn2;
+  if (store && quad == 0) *part_lse = (mrow + fast_log2(lt)) * kLn2;
   return true;
 }
 
@@ -401,8 +402,24 @@ __device__ void prefix_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
       qrow = static_cast<const uint16_t*>(a.q) + (size_t)rowid * D;
       part = clamp_part(rowid * a.view.parts_per_row + c, a.view.max_parts);
     }
-    attend_pages<D, FP8, 1>(a, h, bt, cdiv(ntok, kPage), ntok, qrow, 0, part, vt);
+    attend_pages<D, FP8, 1>(a, h, bt, cdiv(ntok, kPage), ntok, qrow, 0, a.view.part_o + (size_t)part * D,
+                            a.view.part_lse + part, vt);
   }
+}
+
+// The NREP query rows of sequence s and kv-head h over the ntok > 0 tokens of
+// block table bt; columns are copies r16 / NREP of query row r16 % NREP, and
+// part_o, part_lse the lane's row's.
+template <int D, int NREP, bool FP8>
+__device__ __forceinline__ void attend_rows(const AttnArgs& a, int s, int h, const int* bt, int ntok, float* part_o,
+                                            float* part_lse, uint16_t* vt) {
+  const int r16 = threadIdx.x & 15;
+  const uint16_t* qrow =
+      static_cast<const uint16_t*>(a.q) + ((size_t)s * a.num_q_heads + h * NREP + r16 % NREP) * D;
+  bool third = true;
+  while (!attend_pages<D, FP8, 16 / NREP>(a, h, bt, cdiv(ntok, kPage), ntok, qrow, r16 / NREP, part_o, part_lse, vt,
+                                          third))
+    third = false;
 }
 
 // One response unit: kv-head h of response item `item`.
@@ -416,14 +433,9 @@ __device__ void resp_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
   const int slot = min(max(m.w, 0), a.view.parts_per_row - 1);
   if (ntok == 0) return;
   const int* bt = a.resp_block_table + (size_t)s * a.max_resp_pages + p0;
-  // Columns: copy r16 / NREP of query row r16 % NREP.
-  const int r16 = threadIdx.x & 15, rep = r16 % NREP;
-  const int rowid = s * a.num_q_heads + h * NREP + rep;
+  const int rowid = s * a.num_q_heads + h * NREP + (threadIdx.x & 15) % NREP;
   const int part = clamp_part(rowid * a.view.parts_per_row + slot, a.view.max_parts);
-  const uint16_t* qrow = static_cast<const uint16_t*>(a.q) + (size_t)rowid * D;
-  bool third = true;
-  while (!attend_pages<D, FP8, 16 / NREP>(a, h, bt, cdiv(ntok, kPage), ntok, qrow, r16 / NREP, part, vt, third))
-    third = false;
+  attend_rows<D, NREP, FP8>(a, s, h, bt, ntok, a.view.part_o + (size_t)part * D, a.view.part_lse + part, vt);
 }
 
 // All partial results in one launch, one unit per workgroup: the first
@@ -467,6 +479,84 @@ __global__ __launch_bounds__(64) void attn_parts_kernel(const AttnArgs a) {
   }
 }
 
+// A small batch whole, in one launch: a workgroup per (sequence, kv-head)
+// splits the prefix and the response pages into at most kSmallWaves pieces, a
+// wave each, and merges their partials in LDS; each sequence reads its
+// group's prefix for itself (from L2 after the first). Block 0 makes the
+// batch's plan, as the three-launch form leaves it in the workspace. Bound by
+// the chain of round trips and steps of one wave (4 sequences of 192 tokens, 2
+// kv-heads: 8.2 us a call, three launches 13.2).
+template <int D, int NREP, bool FP8>
+__global__ __launch_bounds__(64 * kSmallWaves) void attn_small_kernel(const AttnArgs a, const PlanArgs p, uint16_t* out,
+                                                                      float* lse_out) {
+  constexpr int kStage = Geom<D, FP8>::STAGE_BYTES / 2;
+  struct Work {
+    uint16_t vt[kSmallWaves][kStage];
+    float o[kSmallWaves][NREP][D];
+    float lse[kSmallWaves][NREP];
+  };
+  __shared__ __attribute__((aligned(16))) union Smem {
+    Work w;
+    int cnt[kPlanMaxGroups];
+    __device__ Smem() {}
+  } sm;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < 64) plan_small(p, sm.cnt);
+    return;
+  }
+  const int Hkv = a.num_kv_heads;
+  const int s = (int)(blockIdx.x - 1) / Hkv, h = (int)(blockIdx.x - 1) - s * Hkv;
+  const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int g = clamp_group(a.seq_to_group[s], a.num_groups);
+  const int L = clamp_len(a.resp_lens[s], a.max_resp_pages), P = clamp_len(a.prefix_lens[g], a.max_prefix_pages);
+  // Pieces of `per` pages, of the prefix first: cdiv(x, per) + cdiv(y, per) is
+  // at most kSmallWaves for x + y <= (kSmallWaves - 1) per.
+  const int np = cdiv(P, kPage), nr = cdiv(L, kPage), step = Geom<D, FP8>::PAGES;
+  const int per = cdiv(max(cdiv(np + nr, kSmallWaves - 1), 1), step) * step;
+  const int pre = cdiv(np, per), parts = pre + cdiv(nr, per);
+  if (wave < parts) {
+    const bool in_prefix = wave < pre;
+    const int p0 = (in_prefix ? wave : wave - pre) * per;
+    const int ntok = min(per * kPage, (in_prefix ? P : L) - p0 * kPage);
+    const int* bt = in_prefix ? a.prefix_block_table + (size_t)g * a.max_prefix_pages
+                              : a.resp_block_table + (size_t)s * a.max_resp_pages;
+    const int rep = (t & 15) % NREP;
+    attend_rows<D, NREP, FP8>(a, s, h, bt + p0, ntok, sm.w.o[wave][rep], &sm.w.lse[wave][rep], sm.w.vt[wave]);
+  }
+  __syncthreads();
+  for (int i = t; i < NREP * D / 2; i += 64 * kSmallWaves) {
+    const int rep = i / (D / 2), col = i % (D / 2) * 2;
+    float mx = -INFINITY;
+    for (int k = 0; k < parts; ++k) mx = fmaxf(mx, sm.w.lse[k][rep]);
+    float x = 0.f, y = 0.f, wsum = 0.f;
+    for (int k = 0; k < parts && mx != -INFINITY; ++k) {
+      const float l = sm.w.lse[k][rep];
+      if (l == -INFINITY) continue;  // an empty part, as the combine reads it
+      const float w = fast_exp2((l - mx) * kLog2e);
+      wsum += w;
+      x = fmaf(w, sm.w.o[k][rep][col], x);
+      y = fmaf(w, sm.w.o[k][rep][col + 1], y);
+    }
+    const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
+    const size_t row = (size_t)s * a.num_q_heads + h * NREP + rep;
+    *reinterpret_cast<uint32_t*>(out + row * D + col) = pack_bf16x2(x * inv, y * inv);
+    if (lse_out != nullptr && col == 0) lse_out[row] = wsum > 0.f ? mx + fast_log2(wsum) * kLn2 : -INFINITY;
+  }
+}
+
+template <int D, bool FP8>
+hipError_t small_by_nrep(const AttnArgs& a, const PlanArgs& p, int n_rep, uint16_t* out, float* lse, hipStream_t st) {
+  const dim3 grid((unsigned)(a.num_seqs * a.num_kv_heads + 1)), block(64 * kSmallWaves);
+  switch (n_rep) {
+    case 1: attn_small_kernel<D, 1, FP8><<<grid, block, 0, st>>>(a, p, out, lse); break;
+    case 2: attn_small_kernel<D, 2, FP8><<<grid, block, 0, st>>>(a, p, out, lse); break;
+    case 4: attn_small_kernel<D, 4, FP8><<<grid, block, 0, st>>>(a, p, out, lse); break;
+    case 8: attn_small_kernel<D, 8, FP8><<<grid, block, 0, st>>>(a, p, out, lse); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 // Grid: one block per unit of the largest plan that fits the workspace.
 template <int D, int NREP, bool FP8>
 hipError_t launch_one(const AttnArgs& a, long long prefix_blocks, long long resp_blocks, hipStream_t st) {
@@ -487,6 +577,16 @@ hipError_t by_nrep(const AttnArgs& a, int n_rep, long long pb, long long rb, hip
 }
 
 }  // namespace
+
+hipError_t launch_attn_small(const AttnArgs& a, const PlanArgs& p, int head_dim, int n_rep, bool fp8, void* out,
+                             float* lse, hipStream_t stream) {
+  if (a.num_seqs <= 0) return hipSuccess;
+  if (a.num_seqs > kSmallPlanMaxSeqs || p.num_seqs != a.num_seqs) return hipErrorInvalidValue;
+  uint16_t* o = static_cast<uint16_t*>(out);
+  if (head_dim == 128) return fp8 ? small_by_nrep<128, true>(a, p, n_rep, o, lse, stream) : small_by_nrep<128, false>(a, p, n_rep, o, lse, stream);
+  if (head_dim == 64) return fp8 ? small_by_nrep<64, true>(a, p, n_rep, o, lse, stream) : small_by_nrep<64, false>(a, p, n_rep, o, lse, stream);
+  return hipErrorInvalidValue;
+}
 
 hipError_t launch_attn_parts(const AttnArgs& a, int head_dim, int n_rep, bool fp8, long long max_prefix_items,
                              long long max_resp_items, hipStream_t stream) {

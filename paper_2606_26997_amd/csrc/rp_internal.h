@@ -159,6 +159,10 @@ hipError_t launch_qk_prep_plan(QkPrepArgs a, const PlanArgs& p, int head_dim, bo
 // Grid sizes are upper bounds from host scalars; idle waves exit at once.
 hipError_t launch_attn_parts(const AttnArgs& a, int head_dim, int n_rep, bool fp8, long long max_prefix_items,
                              long long max_resp_items, hipStream_t stream);
+// The whole attention of a small batch, and its plan, in one launch (at most
+// 64 sequences).
+hipError_t launch_attn_small(const AttnArgs& a, const PlanArgs& p, int head_dim, int n_rep, bool fp8, void* out,
+                             float* lse, hipStream_t stream);
 hipError_t launch_combine(const CombineArgs& a, int head_dim, hipStream_t stream);
 hipError_t launch_append(const AppendArgs& a, int head_dim, bool fp8, hipStream_t stream);
 hipError_t launch_prefill_kv_write(const PrefillArgs& a, int head_dim, bool fp8, hipStream_t stream);

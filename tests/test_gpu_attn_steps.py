@@ -56,17 +56,24 @@ def test_partials_keep_fp32_precision(nrep, d, dt):
     assert (np.abs(out - ref) / mag).max() <= 3e-5
 
 
+def _staged(b):
+    b.plan()
+    b.attn_parts()
+    b.combine_parts()
+
+
+@pytest.mark.parametrize("staged", [False, True], ids=["one-launch", "staged"])
 @pytest.mark.parametrize("nrep", [1, 2, 4, 8])
-def test_infinite_and_nan_values_stay_in_their_column(nrep):
+def test_infinite_and_nan_values_stay_in_their_column(nrep, staged):
     import paper_2606_26997_amd as rp
-    print(f"[case] inf/nan nrep {nrep}", flush=True)
+    print(f"[case] inf/nan nrep {nrep} staged {staged}", flush=True)
     wl = make_workload(num_q_heads=2 * nrep, num_kv_heads=2, head_dim=128, seq_to_group=[0, 0], prefix_lens=[0],
                        resp_lens=[40, 21], seed=5)
     page = int(wl.resp_block_table[0, 1])
     for col, bits in ((7, 0x7F80), (64, 0xFF80), (100, 0x7FC0)):
         wl.v_pages[page, 1, 3, col] = bits
     b = rp.DeviceBatch.from_workload(wl)
-    b.attention()
+    _staged(b) if staged else b.attention()
     torch.cuda.synchronize()
     out = b.out.float().cpu().numpy()
     assert np.all(out[0, nrep:, 7] == np.inf) and np.all(out[0, nrep:, 64] == -np.inf)
@@ -86,7 +93,53 @@ def test_fp8_unit_order_covers_every_unit(hkv, lens):
                        prefix_lens=[18], resp_lens=lens, seed=hkv, kv_dtype="fp8")
     b = rp.DeviceBatch.from_workload(wl)
     b.workspace.fill_(0xFF)  # NaN partials: a unit left out shows
-    b.attention()
+    _staged(b)
     out, lse = to_host_out(b)
     ref, ref_lse = oracle.attention_for_workload(wl)
     compare(out, lse, ref, ref_lse, "fp8", f"order-{hkv}")
+
+
+# (Hq, Hkv, d, dtype, groups' prefix lengths, group of each sequence, response lengths): batches on both
+# sides of the line between one launch and three (64 sequences; 70 pages in the tables at 128-wide bf16
+# heads, 140 at half the bytes, twice that from four query rows per kv-head), pieces that end with the
+# prefix, with a page and inside a step, empty prefixes and responses.
+SMALL = [
+    (4, 2, 64, "bf16", [128], [0] * 4, [32, 43, 54, 64]),
+    (16, 8, 128, "bf16", [17, 0, 130], [0, 0, 1, 1, 2], [0, 1, 0, 16, 300]),
+    (8, 8, 128, "bf16", [560, 1], [0, 1, 0], [559, 560, 3]),          # 70 pages
+    (8, 8, 128, "bf16", [560, 1], [0, 1, 0], [559, 561, 3]),          # 71: three launches
+    (6, 3, 64, "fp8", [40, 1200], [0, 1, 1, 0], [1000, 7, 33, 0]),    # 138 pages of 1 KiB
+    (16, 2, 128, "fp8", [300, 90], [0] * 5 + [1] * 3, [5, 900, 64, 63, 65, 0, 129, 800]),
+    (8, 1, 128, "bf16", [1000], [0, 0], [1200, 1]),                   # 138 of at most 140 pages
+    (4, 2, 64, "bf16", [20, 33], [i % 2 for i in range(64)], [3 * i for i in range(64)]),
+    (4, 2, 64, "bf16", [20, 33], [i % 2 for i in range(65)], [3 * i for i in range(65)]),  # three launches
+]
+
+
+@pytest.mark.parametrize("case", range(len(SMALL)))
+def test_one_launch_and_staged_match_the_oracle_and_each_other(case):
+    import paper_2606_26997_amd as rp
+    from tests.gpu_util import compare, to_host_out
+    hq, hkv, d, dt, P, s2g, L = SMALL[case]
+    print(f"[case] small {case}", flush=True)
+    wl = make_workload(num_q_heads=hq, num_kv_heads=hkv, head_dim=d, seq_to_group=s2g, prefix_lens=P, resp_lens=L,
+                       seed=case, kv_dtype=dt)
+    ref, ref_lse = oracle.attention_for_workload(wl)
+    b = rp.DeviceBatch.from_workload(wl)
+    b.workspace.fill_(0xFF)
+    b.attention()
+    out, lse = to_host_out(b)
+    compare(out, lse, ref, ref_lse, dt, f"one call {case}")
+    plan = b.plan_contents()
+    _staged(b)
+    out2, lse2 = to_host_out(b)
+    compare(out2, lse2, ref, ref_lse, dt, f"staged {case}")
+    fin = np.isfinite(ref_lse)
+    assert np.abs(lse[fin] - lse2[fin]).max() <= 3e-5
+    # The one call leaves the plan behind (pieces of equal length may be listed in any order).
+    want = b.plan_contents()
+    assert np.array_equal(plan["hdr"][:4], want["hdr"][:4])
+    for key in ("grp_off", "prefix_items", "seq_parts"):
+        assert np.array_equal(plan[key], want[key]), key
+    order = lambda x: x[np.lexsort(x.T)]
+    assert np.array_equal(order(plan["resp_items"]), order(want["resp_items"]))
