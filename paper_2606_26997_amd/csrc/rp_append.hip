@@ -38,8 +38,7 @@ __global__ __launch_bounds__(64) void append_fp8_kernel(const AppendArgs a) {
   const int s = blockIdx.x / Hkv, h = blockIdx.x - s * Hkv;
   const int L = a.resp_lens[s];
   if (L < 0 || L >= a.max_resp_pages * kPage) return;  // no slot for the new token
-  const int lane = threadIdx.x, v = lane / G, l = lane % G;
-  if (v > 1) return;
+  const int lane = threadIdx.x, v = lane / G & 1, l = lane % G;
   const uint16_t* src = static_cast<const uint16_t*>(v ? a.v_new : a.k_new) + ((size_t)s * Hkv + h) * D;
   const uint2 w = *reinterpret_cast<const uint2*>(src + l * 4);
   const int page = clamp_page(a.resp_block_table[(size_t)s * a.max_resp_pages + L / kPage], a.num_pages);
@@ -47,8 +46,11 @@ __global__ __launch_bounds__(64) void append_fp8_kernel(const AppendArgs a) {
   float* scale = (v ? a.v_scale : a.k_scale) + slot;
   const float x[4] = {bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y)};
   const int col[1] = {l * 4};
-  append_fp8_row<D, G, 4>(static_cast<uint8_t*>(v ? a.v_pages : a.k_pages) + slot * (kPage * D), scale, *scale,
-                          L % kPage, x, col, l == 0);
+  RequantJob job = {};
+  if (lane < 2 * G)
+    job = append_fp8_row<D, G, 4>(static_cast<uint8_t*>(v ? a.v_pages : a.k_pages) + slot * (kPage * D), scale, *scale,
+                                  L % kPage, x, col, l == 0);
+  requantise_fp8_rows<D>(job, l == 0, lane);
 }
 
 // Layout checker (test utility): records the number of bad entries and one example.

@@ -260,16 +260,26 @@ __device__ inline float wave_max(float x) { return max_xor16_32(group_max16(x));
 // `old` is the block's scale (its value does not matter for r = 0); `leader`
 // marks the one lane that stores the new one. amax = max |x| over the row; row
 // 0 sets scale = amax / 448 (1 when amax is 0); a later row keeps the old
-// scale when amax <= 448 * old, and otherwise sets scale = amax / 448 after
-// requantising rows 0..r-1 from code * old. Plain IEEE fp32 (no contraction,
-// quotients as the division rounds them), so the bytes are a deterministic
-// function of the inputs. Every lane of a G-lane group must call it, with the
-// same r.
+// scale when amax <= 448 * old, and otherwise sets scale = amax / 448 and has
+// rows 0..r-1 requantised from code * old: append_fp8_row returns that as a
+// job, which requantise_fp8_rows must do next. Plain IEEE fp32 (no
+// contraction, quotients as the division rounds them), so the bytes are a
+// deterministic function of the inputs. Every lane of a G-lane group must call
+// append_fp8_row, with the same r.
 //
-// The rule is a chain of memory round trips, so callers load `old` early, and
-// the requantised rows come in whole words, eight rows per round trip (one
-// byte a load, the page and its scale loaded after the rotation: 1024
-// sequences' prep into fp8 pages 24.4 us; this way 13.4).
+// The rule is a chain of memory round trips and then bound by the requantised
+// values (about 12 instructions each), so callers load `old` early and the
+// whole wave shares a block's rows, in 8-byte words: about one new row in
+// seven raises its page's scale, so a wave mostly has one job or none, and the
+// lanes of its other rows would wait. (Prep of 1024 sequences into fp8 pages:
+// single bytes and a late scale 24.4 us, whole words by the row's own 16 lanes
+// 13.3, this way 11.3.)
+struct RequantJob {
+  uint8_t* blk;
+  float old, scale;
+  int rows;  // 0: nothing to do
+};
+
 template <int CH, int N>
 __device__ inline void put_codes(uint8_t* row, const int (&col)[N / CH], const uint32_t (&w)[N / 4]) {
 #pragma unroll
@@ -278,18 +288,9 @@ __device__ inline void put_codes(uint8_t* row, const int (&col)[N / CH], const u
     else *reinterpret_cast<uint16_t*>(row + col[k]) = (uint16_t)(w[k / 2] >> (16 * (k % 2)));
   }
 }
-template <int CH, int N>
-__device__ inline void get_codes(const uint8_t* row, const int (&col)[N / CH], uint32_t (&w)[N / 4]) {
-#pragma unroll
-  for (int k = 0; k < N / CH; ++k) {
-    if constexpr (CH == 4) w[k] = *reinterpret_cast<const uint32_t*>(row + col[k]);
-    else if (k % 2 == 0) w[k / 2] = *reinterpret_cast<const uint16_t*>(row + col[k]);
-    else w[k / 2] |= (uint32_t)*reinterpret_cast<const uint16_t*>(row + col[k]) << 16;
-  }
-}
 template <int D, int G, int CH, int N>
-__device__ void append_fp8_row(uint8_t* blk, float* scale_slot, float old, int r, const float (&x)[N],
-                               const int (&col)[N / CH], bool leader) {
+__device__ RequantJob append_fp8_row(uint8_t* blk, float* scale_slot, float old, int r, const float (&x)[N],
+                                     const int (&col)[N / CH], bool leader) {
 #pragma clang fp contract(off)
   static_assert(G == 16 || G == 32, "lanes per row");
   static_assert(CH == 4 || (CH == 2 && N % 4 == 0), "columns per run");
@@ -302,46 +303,81 @@ __device__ void append_fp8_row(uint8_t* blk, float* scale_slot, float old, int r
   }
   amax = group_max16(amax);
   if constexpr (G == 32) amax = max_xor16(amax);
-  float scale;
+  RequantJob job = {blk, old, old, 0};
   if (r == 0) {
-    scale = amax > 0.f ? amax / 448.0f : 1.0f;
-  } else if (amax <= 448.0f * old) {
-    scale = old;
-  } else {
-    scale = amax / 448.0f;
-    const float inv = 1.0f / scale;
-    const bool scales = plain_scale(scale) && plain_scale(old);
-    constexpr int kRows = 8;
-    for (int r0 = 0; r0 < r; r0 += kRows) {
-      uint32_t c[kRows][N / 4];
-#pragma unroll
-      for (int k = 0; k < kRows; ++k)
-        if (r0 + k < r) get_codes<CH, N>(blk + (size_t)(r0 + k) * D, col, c[k]);
-#pragma unroll
-      for (int k = 0; k < kRows; ++k) {
-        if (r0 + k >= r) break;
-        float y[N];
-        uint32_t nan = 0;  // bytes with the NaN code carry into their top bit
-#pragma unroll
-        for (int i = 0; i < N / 4; ++i) {
-          nan |= (c[k][i] & 0x7F7F7F7Fu) + 0x01010101u;
-          const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)c[k][i], false);
-          const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)c[k][i], true);
-          y[4 * i] = lo[0] * old;
-          y[4 * i + 1] = lo[1] * old;
-          y[4 * i + 2] = hi[0] * old;
-          y[4 * i + 3] = hi[1] * old;
-        }
-        uint32_t w[N / 4];
-        e4m3_quotients(y, scale, inv, scales && (nan & 0x80808080u) == 0, w);
-        put_codes<CH, N>(blk + (size_t)(r0 + k) * D, col, w);
-      }
-    }
+    job.scale = amax > 0.f ? amax / 448.0f : 1.0f;
+  } else if (!(amax <= 448.0f * old)) {
+    job.scale = amax / 448.0f;
+    job.rows = r;
   }
   uint32_t w[N / 4];
-  e4m3_quotients(x, scale, 1.0f / scale, plain && plain_scale(scale), w);
+  e4m3_quotients(x, job.scale, 1.0f / job.scale, plain && plain_scale(job.scale), w);
   put_codes<CH, N>(blk + (size_t)r * D, col, w);
-  if (leader) *scale_slot = scale;
+  if (leader) *scale_slot = job.scale;
+  return job;
+}
+
+// Does the jobs of the lanes marked `leader`, one after the other, with every
+// lane of the wave (all of them must call it): the next job's rows are loaded
+// while one is requantised.
+template <int D>
+__device__ inline void requantise_fp8_rows(const RequantJob& job, bool leader, int lane) {
+#pragma clang fp contract(off)
+  constexpr int LPR = D / 8, RPI = 64 / LPR, LOADS = kPage / RPI;  // lanes per row, rows per load, loads per block
+  unsigned long long todo = __ballot(leader && job.rows > 0);
+  if (todo == 0) return;
+  const int row0 = lane / LPR, off = lane * 8;
+  const auto blk_of = [&](int src) __attribute__((always_inline)) {
+    const uint64_t p = reinterpret_cast<uint64_t>(job.blk);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)p, src);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(p >> 32), src);
+    return reinterpret_cast<uint8_t*>((uint64_t)hi << 32 | lo) + off;
+  };
+  const auto load = [&](int src, uint2 (&c)[LOADS]) __attribute__((always_inline)) {
+    const uint8_t* b = blk_of(src);
+    const int rows = __builtin_amdgcn_readlane(job.rows, src);
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i)
+      if (row0 + i * RPI < rows) c[i] = *reinterpret_cast<const uint2*>(b + i * RPI * D);
+  };
+  uint2 cur[LOADS] = {}, next[LOADS] = {};
+  int src = __builtin_ctzll(todo);
+  load(src, cur);
+  while (true) {
+    todo &= todo - 1;
+    const int after = todo != 0 ? __builtin_ctzll(todo) : -1;
+    if (after >= 0) load(after, next);
+    uint8_t* b = blk_of(src);
+    const int rows = __builtin_amdgcn_readlane(job.rows, src);
+    const float old = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(job.old), src));
+    const float scale = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(job.scale), src));
+    const float inv = 1.0f / scale;
+    const bool scales = plain_scale(scale) && plain_scale(old);
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      if (row0 + i * RPI >= rows) continue;
+      const uint32_t c[2] = {cur[i].x, cur[i].y};
+      float y[8];
+      uint32_t nan = 0;  // bytes with the NaN code carry into their top bit
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        nan |= (c[k] & 0x7F7F7F7Fu) + 0x01010101u;
+        const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)c[k], false);
+        const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)c[k], true);
+        y[4 * k] = lo[0] * old;
+        y[4 * k + 1] = lo[1] * old;
+        y[4 * k + 2] = hi[0] * old;
+        y[4 * k + 3] = hi[1] * old;
+      }
+      uint32_t w[2];
+      e4m3_quotients(y, scale, inv, scales && (nan & 0x80808080u) == 0, w);
+      *reinterpret_cast<uint2*>(b + i * RPI * D) = make_uint2(w[0], w[1]);
+    }
+    if (after < 0) return;
+    src = after;
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) cur[i] = next[i];
+  }
 }
 
 // MFMA tiles used by the group-prefix and prefill paths (fp32 accumulate).

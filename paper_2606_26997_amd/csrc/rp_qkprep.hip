@@ -76,8 +76,9 @@ struct AppendAt {
   int row;
 };
 
+// One head slot; returns the requantisation that its append leaves to do.
 template <int D, bool FP8>
-__device__ inline void prep_slot(const QkPrepArgs& a, int s, int kind, int head, int l16, const AppendAt& at,
+__device__ inline RequantJob prep_slot(const QkPrepArgs& a, int s, int kind, int head, int l16, const AppendAt& at,
                                  float old_scale,
                                  const uint32_t (&x1)[D / 64], const uint32_t (&x2)[D / 64],
                                  const double (*s_tab)[4][D / 2]) {
@@ -140,7 +141,7 @@ __device__ inline void prep_slot(const QkPrepArgs& a, int s, int kind, int head,
       uint16_t* dst = a.q_out + ((size_t)s * Hq + head) * D;
       store_words<W>(dst, c1, o1);
       store_words<W>(dst, c2, o2);
-      return;
+      return RequantJob{};
     }
     if (a.k_out != nullptr) {
       uint16_t* dst = a.k_out + ((size_t)s * Hkv + head) * D;
@@ -150,12 +151,13 @@ __device__ inline void prep_slot(const QkPrepArgs& a, int s, int kind, int head,
   }
 
   // Append of k (kind 1) or v (kind 2) at response slot L.
-  if (at.slot < 0) return;  // no slot for the new token
+  if (at.slot < 0) return RequantJob{};  // no slot for the new token
   const size_t blk = ((size_t)at.slot + head) * kPage * D;  // in elements
   if constexpr (!FP8) {
     uint16_t* dst = static_cast<uint16_t*>(kind == 1 ? a.k_pages : a.v_pages) + blk + (size_t)at.row * D;
     store_words<W>(dst, c1, o1);
     store_words<W>(dst, c2, o2);
+    return RequantJob{};
   } else {
     float xf[2 * NP];
 #pragma unroll
@@ -164,9 +166,9 @@ __device__ inline void prep_slot(const QkPrepArgs& a, int s, int kind, int head,
       xf[NP + p] = p & 1 ? bf16_hi(o2[p >> 1]) : bf16_lo(o2[p >> 1]);
     }
     const int col[2] = {c1, c2};
-    append_fp8_row<D, kSlotLanes, NP>(static_cast<uint8_t*>(kind == 1 ? a.k_pages : a.v_pages) + blk,
-                                      (kind == 1 ? a.k_scale : a.v_scale) + at.slot + head, old_scale, at.row, xf, col,
-                                      l16 == 0);
+    return append_fp8_row<D, kSlotLanes, NP>(static_cast<uint8_t*>(kind == 1 ? a.k_pages : a.v_pages) + blk,
+                                             (kind == 1 ? a.k_scale : a.v_scale) + at.slot + head, old_scale, at.row,
+                                             xf, col, l16 == 0);
   }
 }
 
@@ -237,7 +239,9 @@ __device__ __forceinline__ void prep_block(const QkPrepArgs& a, int bid, PrepTab
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < SPL; ++k) {
-    if (kind[k] < 3) prep_slot<D, FP8>(a, s, kind[k], head[k], l16, at, old_scale[k], x1[k], x2[k], s_tab);
+    RequantJob job = {};
+    if (kind[k] < 3) job = prep_slot<D, FP8>(a, s, kind[k], head[k], l16, at, old_scale[k], x1[k], x2[k], s_tab);
+    if constexpr (FP8) requantise_fp8_rows<D>(job, l16 == 0, t & 63);
   }
 }
 
