@@ -41,8 +41,8 @@
 namespace rp {
 namespace {
 
-// V pages are read with the non-temporal hint and K pages without it: both
-// streams are read exactly once, and marking one of the two (either one) as
+// V pages of responses are read with the non-temporal hint and K pages without
+// it: both streams are read exactly once, and marking one of the two (either one) as
 // streaming was measured 6-8% faster on every workload than marking neither
 // or both.
 // Loaded pages are held in clang vectors: HIP's uint4 is copied through
@@ -127,8 +127,9 @@ __device__ inline void stage_v(const u32x4_t (&v)[Geom<D, FP8>::LOADS], int nval
 // COPIES = 2, lo takes a second product on hi's column if `third`; an infinite
 // v then makes the column NaN (0 times infinity), and the result false: the
 // caller runs the pages again without it. The lanes of term 0 write the row's
-// partial to part_o [D] and part_lse.
-template <int D, bool FP8, int COPIES>
+// partial to part_o [D] and part_lse. REUSE: the pages are read again by a
+// later pass, so V too is loaded without the non-temporal hint.
+template <int D, bool FP8, int COPIES, bool REUSE>
 __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int* bt, int npages, int ntok,
                                              const uint16_t* qrow, int term, float* part_o, float* part_lse, uint16_t* vt,
                                              bool third = true) {
@@ -200,7 +201,8 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
     for (int i = 0; i < PAGES; ++i) {
       const char* b = vpool + block(p + i);
 #pragma unroll
-      for (int j = 0; j < LOADS; ++j) vx[i][j] = load_v_stream(b + voff + j * 1024);
+      for (int j = 0; j < LOADS; ++j)
+        vx[i][j] = REUSE ? *reinterpret_cast<const u32x4_t*>(b + voff + j * 1024) : load_v_stream(b + voff + j * 1024);
     }
   };
   load_k(0);
@@ -378,7 +380,10 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
 // One group-prefix unit: kv-head h of (group, chunk of prefix pages), for all
 // query rows of the group's live members, 16 rows per pass. A group with more
 // than 16 query rows reads the chunk again for each further pass; the chunk
-// (a few tens of KiB) is then still in this XCD's L2.
+// (a few tens of KiB) is then still in this XCD's L2, its V too, since prefix
+// units load it without the non-temporal hint (64 rows a group, Hq 32, Hkv 4,
+// 256 sequences: 395.9 us a step with the hint, 392.2 without; 16 rows 367 both
+// ways).
 template <int D, int NREP, bool FP8>
 __device__ void prefix_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
   const int2 it = a.view.prefix_items[item];
@@ -402,8 +407,8 @@ __device__ void prefix_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
       qrow = static_cast<const uint16_t*>(a.q) + (size_t)rowid * D;
       part = clamp_part(rowid * a.view.parts_per_row + c, a.view.max_parts);
     }
-    attend_pages<D, FP8, 1>(a, h, bt, cdiv(ntok, kPage), ntok, qrow, 0, a.view.part_o + (size_t)part * D,
-                            a.view.part_lse + part, vt);
+    attend_pages<D, FP8, 1, true>(a, h, bt, cdiv(ntok, kPage), ntok, qrow, 0, a.view.part_o + (size_t)part * D,
+                                  a.view.part_lse + part, vt);
   }
 }
 
@@ -417,7 +422,7 @@ __device__ __forceinline__ void attend_rows(const AttnArgs& a, int s, int h, con
   const uint16_t* qrow =
       static_cast<const uint16_t*>(a.q) + ((size_t)s * a.num_q_heads + h * NREP + r16 % NREP) * D;
   bool third = true;
-  while (!attend_pages<D, FP8, 16 / NREP>(a, h, bt, cdiv(ntok, kPage), ntok, qrow, r16 / NREP, part_o, part_lse, vt,
+  while (!attend_pages<D, FP8, 16 / NREP, false>(a, h, bt, cdiv(ntok, kPage), ntok, qrow, r16 / NREP, part_o, part_lse, vt,
                                           third))
     third = false;
 }
