@@ -349,8 +349,8 @@ def prefill_bench(args):
         nbytes += int(((P64 + 15) // 16).sum()) * Hkv * 8
     # Causal attention flops: QK and PV over the u <= t pairs (2 flops per multiply-add).
     flops = int((P64 * (P64 + 1) // 2).sum()) * Hq * d * 4
-    # One step is rp_prefill: for a bf16 pool a single launch of the attention
-    # kernel that also writes the pages; for fp8 the page-write kernel first.
+    # One step is rp_prefill: a single launch of the attention kernel, which also
+    # writes the pages.
     for _ in range(args.warmup):
         b.prefill()
     torch.cuda.synchronize()

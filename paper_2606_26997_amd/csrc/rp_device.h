@@ -199,18 +199,6 @@ constexpr int kRowHalfMirror = 0x141;
 constexpr int kRowMirror = 0x140;
 constexpr int kRowShl = 0x100;       // + n: lane i of a row of 16 reads lane i + n
 
-// Sum over aligned groups of N lanes (N in {4, 8, 16}); every lane of a group
-// gets the same, bitwise identical, total.
-template <int N>
-__device__ inline float group_sum(float x) {
-  static_assert(N == 4 || N == 8 || N == 16, "group size");
-  x += dpp<kQuadSwap1>(x);
-  x += dpp<kQuadSwap2>(x);
-  if constexpr (N >= 8) x += dpp<kRowHalfMirror>(x);
-  if constexpr (N >= 16) x += dpp<kRowMirror>(x);
-  return x;
-}
-
 // Butterfly over the lanes that differ only in bits >= log2(FIRST) of the lane id.
 template <int FIRST>
 __device__ inline float xor_max_from(float x) {
