@@ -124,20 +124,22 @@ __device__ inline void stage_v(const u32x4_t (&v)[Geom<D, FP8>::LOADS], int nval
 // probabilities are rounded to bf16. COPIES > 1: each row stands in that many
 // columns, 16 / COPIES lanes apart, and column `term` carries the bf16 term
 // of that index of its fp32 probabilities (p = hi + mid + lo, exactly). With
-// COPIES = 2, lo takes a second product on hi's column if `third`; an infinite
-// v then makes the column NaN (0 times infinity), and the result false: the
-// caller runs the pages again without it. The lanes of term 0 write the row's
+// COPIES = 2, lo takes a second product on hi's column; an infinite v then
+// makes elements NaN (0 times infinity), and the result false: the caller runs
+// the pages AGAIN, without lo, for the elements that came out infinite or NaN
+// alone (the others have all three terms). The lanes of term 0 write the row's
 // partial to part_o [D] and part_lse. REUSE: the pages are read again by a
 // later pass, so V too is loaded without the non-temporal hint.
-template <int D, bool FP8, int COPIES, bool REUSE>
+template <int D, bool FP8, int COPIES, bool REUSE, bool AGAIN = false>
 __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int* bt, int npages, int ntok,
-                                             const uint16_t* qrow, int term, float* part_o, float* part_lse, uint16_t* vt,
-                                             bool third = true) {
+                                             const uint16_t* qrow, int term, float* part_o, float* part_lse,
+                                             uint16_t* vt) {
   using G = Geom<D, FP8>;
   constexpr int EPL = G::EPL, LOADS = G::LOADS, PAGES = G::PAGES, DT = D / 16, PITCH = G::PITCH;
   // Probabilities that are rounded to bf16 keep the true maximum, whose own
   // probability is then exactly 1; exact ones take a lazy maximum.
   constexpr float HEADROOM = COPIES > 1 ? kLazyMax : 0.f;
+  constexpr bool THIRD = COPIES == 2 && !AGAIN;  // lo's own product
   const int Hkv = a.num_kv_heads;
   const int lane = threadIdx.x & 63, r16 = lane & 15, quad = lane >> 4;
   const char* kpool = static_cast<const char*>(a.k_pages);
@@ -300,10 +302,12 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
       } else if constexpr (COPIES == 2) {
         sub4(pw, w, -1.f);
         const uint2 mid = pack4(pw);
-        sub4(pw, mid, -1.f);
-        const uint2 low = pack4(pw);
         w = term == 0 ? w : mid;
-        pop3[i] = __builtin_bit_cast(bf16x4_t, term == 0 ? low : make_uint2(0, 0));
+        if constexpr (THIRD) {
+          sub4(pw, mid, -1.f);
+          const uint2 low = pack4(pw);
+          pop3[i] = __builtin_bit_cast(bf16x4_t, term == 0 ? low : make_uint2(0, 0));
+        }
       }
       pop[i] = __builtin_bit_cast(bf16x4_t, w);
     }
@@ -316,9 +320,7 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
       for (int dt = 0; dt < DT; ++dt) {
         const bf16x4_t vo = lds_read_tr(vtr + dt * 16);
         oacc[dt] = mfma16x16x16(vo, pop[0], oacc[dt]);
-        if constexpr (COPIES == 2) {
-          if (third) oacc[dt] = mfma16x16x16(vo, pop3[0], oacc[dt]);
-        }
+        if constexpr (THIRD) oacc[dt] = mfma16x16x16(vo, pop3[0], oacc[dt]);
       }
     } else {
 #pragma unroll
@@ -330,9 +332,9 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
           const bf16x4_t v1 = lds_read_tr(vtr + (i + 1) * kPage * PITCH + dt * 16);
           const bf16x8_t vo = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
           oacc[dt] = mfma16x16x32(vo, pp, oacc[dt]);
-          if constexpr (COPIES == 2) {
+          if constexpr (THIRD) {
             const bf16x8_t pl = __builtin_shufflevector(pop3[i], pop3[i + 1], 0, 1, 2, 3, 4, 5, 6, 7);
-            if (third) oacc[dt] = mfma16x16x32(vo, pl, oacc[dt]);
+            oacc[dt] = mfma16x16x32(vo, pl, oacc[dt]);
           }
         }
       }
@@ -342,13 +344,14 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
   for (; p + PAGES < npages; p += PAGES) step(p, std::true_type{});
   step(p, std::false_type{});
 
-  if constexpr (COPIES == 2) {
+  bool done = true;
+  if constexpr (THIRD) {
     bool finite = true;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int e = 0; e < 4; ++e) finite = finite && fabsf(oacc[dt][e]) < INFINITY;
-    if (third && !__all(finite)) return false;
+    done = __all(finite);
   }
 
   // Add a row's terms (an infinite first term stands alone: with an infinite
@@ -371,10 +374,18 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
       }
       v[e] *= inv;
     }
-    if (store) *reinterpret_cast<float4*>(dst + dt * 16) = make_float4(v[0], v[1], v[2], v[3]);
+    if (!store) continue;
+    float4* at = reinterpret_cast<float4*>(dst + dt * 16);
+    if constexpr (AGAIN) {  // this lane's own store of the first run
+      const float4 first = *at;
+      const float f[4] = {first.x, first.y, first.z, first.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = fabsf(f[e]) < INFINITY ? f[e] : v[e];
+    }
+    *at = make_float4(v[0], v[1], v[2], v[3]);
   }
-  if (store && quad == 0) *part_lse = (mrow + fast_log2(lt)) * kLn2;
-  return true;
+  if (!AGAIN && store && quad == 0) *part_lse = (mrow + fast_log2(lt)) * kLn2;
+  return done;
 }
 
 // One group-prefix unit: kv-head h of (group, chunk of prefix pages), for all
@@ -421,10 +432,13 @@ __device__ __forceinline__ void attend_rows(const AttnArgs& a, int s, int h, con
   const int r16 = threadIdx.x & 15;
   const uint16_t* qrow =
       static_cast<const uint16_t*>(a.q) + ((size_t)s * a.num_q_heads + h * NREP + r16 % NREP) * D;
-  bool third = true;
-  while (!attend_pages<D, FP8, 16 / NREP, false>(a, h, bt, cdiv(ntok, kPage), ntok, qrow, r16 / NREP, part_o, part_lse, vt,
-                                          third))
-    third = false;
+  const int npages = cdiv(ntok, kPage);
+  const bool done =
+      attend_pages<D, FP8, 16 / NREP, false>(a, h, bt, npages, ntok, qrow, r16 / NREP, part_o, part_lse, vt);
+  if constexpr (NREP == 8) {
+    if (!done)
+      attend_pages<D, FP8, 2, false, true>(a, h, bt, npages, ntok, qrow, r16 / NREP, part_o, part_lse, vt);
+  }
 }
 
 // One response unit: kv-head h of response item `item`.
@@ -454,7 +468,8 @@ __device__ void resp_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
 // counts are clamped to the plan's capacity, so even a workspace that was
 // never planned cannot send a wave outside the item lists.
 template <int D, int NREP, bool FP8>
-__global__ __launch_bounds__(64) void attn_parts_kernel(const AttnArgs a) {
+__global__ __launch_bounds__(64)
+void attn_parts_kernel(const AttnArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t vt[Geom<D, FP8>::STAGE_BYTES / 2];
   const int Hkv = a.num_kv_heads;
   const int n_pre = min(max(a.view.hdr[kHdrPrefixItems], 0), a.view.max_prefix_items) * Hkv;

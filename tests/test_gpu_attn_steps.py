@@ -82,6 +82,46 @@ def test_infinite_and_nan_values_stay_in_their_column(nrep, staged):
     assert np.isfinite(out).all()
 
 
+@pytest.mark.parametrize("d,dt", [(64, "bf16"), (128, "bf16"), (64, "fp8"), (128, "fp8")])
+@pytest.mark.parametrize("nrep", [4, 8])
+def test_infinite_and_nan_values_leave_the_other_elements_alone(nrep, d, dt):
+    """Every element whose values are finite keeps the bits it has without the infinite one: the fp32
+    partials of the staged form, and the output of the one-launch form."""
+    import paper_2606_26997_amd as rp
+    print(f"[case] bits beside inf nrep {nrep} d {d} {dt}", flush=True)
+    wl = make_workload(num_q_heads=2 * nrep, num_kv_heads=2, head_dim=d, seq_to_group=[0, 0], prefix_lens=[0],
+                       resp_lens=[100, 21], seed=6, kv_dtype=dt)
+    marked = copy.copy(wl)
+    marked.v_pages = wl.v_pages.copy()
+    page = int(wl.resp_block_table[0, 1])
+    cols = {9: 0x7FC0, 50: 0x7F80} if dt == "bf16" else {9: 0x7F, 50: 0x7F}  # NaN, infinity; e4m3 has no infinity
+    for c, bits in cols.items():
+        marked.v_pages[page, 1, 3, c] = bits
+    got = []
+    for w in (wl, marked):
+        b = rp.DeviceBatch.from_workload(w)
+        b.workspace.fill_(0xFF)
+        b.plan()
+        b.attn_parts()
+        torch.cuda.synchronize()
+        info = rp._binding.plan_layout(b.kv, b.attn_layout)
+        ws = b.workspace.cpu().numpy()
+        po = ws[info.part_o:info.part_o + 4 * info.max_parts * d].view(np.uint32).reshape(-1, d)
+        pl = ws[info.part_lse:info.part_lse + 4 * info.max_parts].view(np.uint32)
+        b.attention()
+        torch.cuda.synchronize()
+        out = b.out.view(torch.int16).cpu().numpy().reshape(-1, d)
+        got.append((po.copy(), pl.copy(), out, b.lse.cpu().numpy()))
+    for x, y in zip(*got):
+        keep = np.ones(x.shape, bool)
+        if x.ndim == 2 and x.shape[1] == d:
+            keep[:, list(cols)] = False
+        assert np.array_equal(x[keep], y[keep])
+    special = torch.from_numpy(got[1][2][nrep:2 * nrep]).view(torch.bfloat16).float().numpy()
+    assert np.isnan(special[:, 9]).all()
+    assert np.isinf(special[:, 50]).all() if dt == "bf16" else np.isnan(special[:, 50]).all()
+
+
 @pytest.mark.parametrize("hkv,lens", [(1, [40] * 19), (2, [20] * 8), (8, [33] * 9), (3, [700, 16, 5])])
 def test_fp8_unit_order_covers_every_unit(hkv, lens):
     """fp8 units are dealt eight items at a time; batches with a remainder of items, fewer than eight, and
