@@ -192,8 +192,10 @@ rp_status rp_group_decode_attn_workspace_size(const rp_paged_kv* kv,
  *   bytes, 256-byte aligned, used for the work plan and partial results;
  *   concurrent calls need distinct workspaces.
  * Equivalent to rp_plan, rp_attn_parts, rp_combine_parts: the workspace holds
- * the plan afterwards. Small batches (at most 64 sequences whose tables span
- * few pages) take one launch, which keeps its partial results on chip. */
+ * the plan and partial results afterwards, and rp_combine_parts gives out and
+ * lse again. Small batches (at most 64 sequences whose tables span few pages)
+ * take one launch, which merges on chip: the partial results that it leaves
+ * are a row's whole result and empty ones. */
 rp_status rp_group_decode_attn(const rp_paged_kv* kv, const rp_group_layout* layout,
                                const void* q, float softmax_scale, void* out, float* lse,
                                void* workspace, size_t workspace_bytes, hipStream_t stream);

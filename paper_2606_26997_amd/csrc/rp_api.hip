@@ -450,8 +450,8 @@ rp_status rp_group_decode_attn_noalloc(const rp_paged_kv* kv, const rp_group_lay
   void* ws = nullptr;
   st = scratch_address(&ws);
   if (st != RP_OK) return st;
-  // The same three launches as rp_group_decode_attn. The plan overwrites every
-  // entry the attention and combine kernels read, so nothing needs clearing.
+  // The same launches as rp_group_decode_attn. The plan and the partial results
+  // overwrite every entry that is read later, so nothing needs clearing.
   return rp_group_decode_attn(kv, l, q, softmax_scale, out, lse, ws, RP_NOALLOC_SCRATCH_BYTES, stream);
 }
 

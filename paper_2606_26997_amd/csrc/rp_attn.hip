@@ -503,9 +503,10 @@ void attn_parts_kernel(const AttnArgs a) {
 // splits the prefix and the response pages into at most kSmallWaves pieces, a
 // wave each, and merges their partials in LDS; each sequence reads its
 // group's prefix for itself (from L2 after the first). Block 0 makes the
-// batch's plan, as the three-launch form leaves it in the workspace. Bound by
-// the chain of round trips and steps of one wave (4 sequences of 192 tokens, 2
-// kv-heads: 8.2 us a call, three launches 13.2).
+// batch's plan, as the three-launch form leaves it in the workspace, and a
+// row's merged result becomes its first partial there (the others empty), so
+// that a combine on the workspace gives out and lse again. Bound by the chain of round trips and steps of one wave (4 sequences of 192 tokens, 2
+// kv-heads: 8.2 us a call, three launches 13.2; the partials are 0.1 us of it).
 template <int D, int NREP, bool FP8>
 __global__ __launch_bounds__(64 * kSmallWaves) void attn_small_kernel(const AttnArgs a, const PlanArgs p, uint16_t* out,
                                                                       float* lse_out) {
@@ -559,8 +560,19 @@ __global__ __launch_bounds__(64 * kSmallWaves) void attn_small_kernel(const Attn
     }
     const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
     const size_t row = (size_t)s * a.num_q_heads + h * NREP + rep;
-    *reinterpret_cast<uint32_t*>(out + row * D + col) = pack_bf16x2(x * inv, y * inv);
-    if (lse_out != nullptr && col == 0) lse_out[row] = wsum > 0.f ? mx + fast_log2(wsum) * kLn2 : -INFINITY;
+    x *= inv;
+    y *= inv;
+    const float lse = wsum > 0.f ? mx + fast_log2(wsum) * kLn2 : -INFINITY;
+    *reinterpret_cast<uint32_t*>(out + row * D + col) = pack_bf16x2(x, y);
+    if (lse_out != nullptr && col == 0) lse_out[row] = lse;
+    const int slots = a.view.parts_per_row;
+    if (slots == 0) continue;  // tables without pages: no partials
+    const size_t part = row * slots;
+    *reinterpret_cast<float2*>(a.view.part_o + part * D + col) = make_float2(x, y);
+    // The combine gives NaN and an lse of minus infinity, as here, for a part
+    // of lse plus infinity.
+    if (col == 0) a.view.part_lse[part] = wsum != wsum ? INFINITY : lse;
+    for (int k = 1 + col / 2; k < slots; k += D / 2) a.view.part_lse[part + k] = -INFINITY;
   }
 }
 

@@ -183,3 +183,28 @@ def test_one_launch_and_staged_match_the_oracle_and_each_other(case):
         assert np.array_equal(plan[key], want[key]), key
     order = lambda x: x[np.lexsort(x.T)]
     assert np.array_equal(order(plan["resp_items"]), order(want["resp_items"]))
+
+
+@pytest.mark.parametrize("case", range(len(SMALL)))
+def test_combine_after_the_one_call_gives_its_results_again(case):
+    """rp_group_decode_attn leaves partial results that rp_combine_parts merges to the same bits, in the
+    one-launch form too, for rows without keys and rows with NaN scores as well."""
+    import paper_2606_26997_amd as rp
+    hq, hkv, d, dt, P, s2g, L = SMALL[case]
+    print(f"[case] combine again {case}", flush=True)
+    wl = make_workload(num_q_heads=hq, num_kv_heads=hkv, head_dim=d, seq_to_group=s2g, prefix_lens=P, resp_lens=L,
+                       seed=case, kv_dtype=dt)
+    wl.q[-1, 1, 3] = 0x7FC0
+    if dt == "bf16":
+        wl.k_pages[wl.resp_block_table[0, 0], 0, 0, 5] = 0x7FC0  # one NaN key: NaN beside finite parts
+    b = rp.DeviceBatch.from_workload(wl)
+    b.workspace.fill_(0xFF)
+    b.attention()
+    out, lse = b.out.clone(), b.lse.clone()
+    b.out.fill_(7.0)
+    b.lse.fill_(7.0)
+    b.combine_parts()
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isnan(out), torch.isnan(b.out))
+    assert torch.equal(out.nan_to_num(9.0).view(torch.int16), b.out.nan_to_num(9.0).view(torch.int16))
+    assert torch.equal(lse.view(torch.int32), b.lse.view(torch.int32))
