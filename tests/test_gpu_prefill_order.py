@@ -46,6 +46,32 @@ def test_every_row_of_every_order(case):
     assert np.abs(lse - ref_lse).max() <= 1e-4
 
 
+@pytest.mark.parametrize("two_tiles", [False, True], ids=["one-tile", "two-tiles"])
+@pytest.mark.parametrize("nrep", [1, 2, 4, 8])
+@pytest.mark.parametrize("d", [64, 128])
+def test_page_rows_end_with_the_prompt(d, nrep, two_tiles):
+    """bf16 rows that the attention writes into the pages: those of the page-write call, byte for byte, around
+    the ends of a workgroup's rows and of one pass of its threads over them; no row past a prompt's end."""
+    import paper_2606_26997_amd as rp
+    print(f"[case] page rows d {d} nrep {nrep} two tiles {two_tiles}", flush=True)
+    lens = [1, 7, 8, 9, 0, 15, 16, 17, 31, 32, 33, 47, 63, 64, 65, 127, 128, 129]
+    if two_tiles:
+        lens = [511, 513] * 30 + lens
+        assert sum(lens) >= 384 * len(lens)
+    w = make_prefill_workload(num_q_heads=2 * nrep, num_kv_heads=2, head_dim=d, prefix_lens=lens, seed=d + nrep)
+    pools = []
+    for call in ("prefill", "kv_write"):
+        b = rp.PrefillBatch.from_workload(w)
+        for x in (b.k_pages, b.v_pages):
+            x.view(torch.int16).fill_(0x5555)
+        getattr(b, call)()
+        torch.cuda.synchronize()
+        pools.append((b.k_pages.view(torch.int16).clone(), b.v_pages.view(torch.int16).clone()))
+    assert (pools[1][0] == 0x5555).any()  # rows past the ends
+    for x, y in zip(*pools):
+        assert torch.equal(x, y)
+
+
 def test_large_and_hidden_scores():
     """Scores that grow by far more than the lazy maximum's headroom from block to block, and a first key
     block whose scores are all hugely negative: the running maximum has to move at the right blocks."""
