@@ -219,8 +219,20 @@ __device__ inline void pf_load(uint32_t stage, const uint16_t* kbase, const uint
 // number of pairs and an odd `stride` from one set of pairs to the next (one
 // idle workgroup where needed) keep a pair, or a row block, from falling to
 // one engine every time (4 pairs instead of 5 on ragged prompts of 300-1800
-// tokens: 317 us against 208). stride = 0: any NP, pairs dealt in turn.
+// tokens: 317 us against 208). stride = 0: any NP, pairs dealt in turn, which
+// is also the order of small grids.
 constexpr int kPfPairs = 5;
+// Grids up to this many workgroups start nearly all of them at once (four 128-
+// wide or six 64-wide workgroups with one row tile fit a compute unit): there
+// is little left to keep in L2, and the long row blocks of all pairs first
+// spread best over the compute units. Measured, pairs in turn against a few at
+// a time, in us (Hq / Hkv, d, prompts; workgroups):
+//   8 / 8, 128, 32 x U[32, 128]; 512:    10.3, 11.4;  16 x U[300, 400]; 896: 19.8, 21.2
+//   16 / 8, 128, 32 x U[32, 128]; 1024:  13.2, 12.7;  16 x U[300, 400]; 1664: 27.3, 28.2
+//   16 / 8, 128, 64 x U[64, 256]; 4096:  41.6, 36.3;  64 / 8, 8 x U[512, 1024]; 4096: 112, 101
+//   16 / 8, 64, 32 x U[16, 64]; 512:     5.88, 6.29;  64 x U[32, 128]; 2048: 11.4, 12.0
+//   32 / 8, 64, 8 x U[512, 1024]; 2048:  37.5, 40.0;  64 / 8, the same; 4096: 66.1, 59.7
+__host__ inline constexpr long long pf_small_grid(int head_dim) { return 1024 * 128 / head_dim; }
 __host__ __device__ inline int pf_stride(int max_blocks) { return (kPfPairs * max_blocks) | 1; }
 __device__ inline bool pf_unit(int b, int NP, int max_blocks, int stride, int* pair, int* rb) {
   if (stride == 0) {
@@ -529,7 +541,9 @@ hipError_t attn_launch(const PrefillArgs& a, hipStream_t st) {
   const int max_blocks = cdiv(max_tokens, tpb);
   // A launch has at most 2^24 workgroups of 256 threads; the idle ones of the
   // ordered grid must not be what exceeds it.
-  const int stride = NP % 8 == 0 && NP * (max_blocks + 1) < (1ll << 24) ? pf_stride(max_blocks) : 0;
+  const bool ordered =
+      NP % 8 == 0 && NP * max_blocks > pf_small_grid(D) && NP * (max_blocks + 1) < (1ll << 24);
+  const int stride = ordered ? pf_stride(max_blocks) : 0;
   const long long pairs = NP / 8;
   const long long blocks =
       stride == 0 ? NP * max_blocks : 8 * (pairs / kPfPairs * stride + pairs % kPfPairs * max_blocks);

@@ -1,6 +1,7 @@
 """Prefill grids: the order that keeps few (group, kv-head) pairs on an XCD at a time, its remainders, and
-the plain order of pair counts that are no multiple of 8; prompts around the ends of key blocks and
-workgroup rows, one and two row tiles per wave. Every row is compared with the oracle."""
+the plain order of small grids (up to 1024 workgroups, 2048 with 64-wide heads) and of pair counts that
+are no multiple of 8; prompts around the ends of key blocks and workgroup rows, one and two row tiles per
+wave. Every row is compared with the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -12,10 +13,18 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # (name, Hq, Hkv, d, prompt lengths, kv dtype)
-    ("one-set", 16, 8, 128, [33, 64, 31], "bf16"),                       # 3 of 5 pairs per XCD
-    ("two-sets-odd-blocks", 16, 8, 64, [95, 1, 32, 65, 96, 17], "bf16"),  # 5 + 1 pairs, 3 row blocks
+    ("one-set", 16, 8, 128, [33, 64, 31], "bf16"),
+    ("two-sets-odd-blocks", 16, 8, 64, [95, 1, 32, 65, 96, 17], "bf16"),
     ("two-sets-even-blocks", 8, 8, 128, [128, 127, 0, 63, 64, 3, 100], "bf16"),
-    ("half-pairs", 16, 4, 128, [40, 16, 70, 8], "fp8"),                  # 16 pairs from 4 kv-heads
+    ("half-pairs", 16, 4, 128, [40, 16, 70, 8], "fp8"),
+    # Ordered grids: sets of 5 of an XCD's pairs, with a remainder or none, odd and even row blocks.
+    ("ordered-one-set", 64, 8, 128, [345, 337, 344], "bf16"),             # 3 pairs per XCD, 44 row blocks
+    ("ordered-odd-blocks", 32, 8, 128, [5, 17, 33, 40, 0, 16] * 8, "bf16"),  # 48 pairs, 3 row blocks
+    ("ordered-even-blocks", 16, 8, 64, [61, 1, 32, 64, 33] * 26, "bf16"),  # 130 pairs, no remainder
+    ("ordered-fp8", 32, 4, 128, [40, 16, 70, 8] * 8, "fp8"),              # 16 pairs, 10 row blocks
+    ("ordered-two-tiles", 64, 8, 64, [385, 641, 400, 150, 700, 390], "bf16"),
+    ("at-the-line", 8, 8, 128, [64, 63, 17, 0] * 32, "bf16"),             # 1024 workgroups: plain
+    ("over-the-line", 8, 8, 128, [65, 63, 17, 0] * 17, "bf16"),           # 1088
     ("plain-order", 4, 2, 128, [50, 33, 130], "bf16"),                   # 6 pairs
     ("plain-order-nrep8", 8, 1, 64, [20, 45, 64], "bf16"),
     ("two-tiles", 16, 8, 128, [400, 385, 31, 800], "bf16"),              # 404 tokens a prompt
