@@ -478,7 +478,9 @@ void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride) {
   // At a block's start its copies are complete (the wave's own, then, past
   // the barrier, everyone's); with three stages the next block's are in
   // flight, and the one after that is requested into the stage the barrier
-  // has freed.
+  // has freed. With two stages the next block is requested then, except the
+  // second, which goes into the stage that is free from the start (32 prompts
+  // of U[16, 64] at Hq 16, Hkv 8, d 64: 5.6 us without, 5.4 with).
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)smem;
   const int uwave = __builtin_amdgcn_readfirstlane(wave);
   const auto request = [&](int blk, int stage) __attribute__((always_inline)) {
@@ -492,12 +494,12 @@ void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride) {
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(qop[rt][kb]));
-  if (STAGES == 3 && nblk > 1) request(1, 1);
+  if (nblk > 1) request(1, 1);
   int cur = 0;
   for (int blk = 0; blk < nblk; ++blk) {
-    if (STAGES == 3 && blk + 1 < nblk) pf_wait<L::kPerWave>();
+    if ((STAGES == 3 || blk == 0) && blk + 1 < nblk) pf_wait<L::kPerWave>();
     else pf_wait<0>();
-    if (blk + STAGES - 1 < nblk) request(blk + STAGES - 1, cur == 0 ? STAGES - 1 : cur - 1);
+    if ((STAGES == 3 || blk > 0) && blk + STAGES - 1 < nblk) request(blk + STAGES - 1, cur == 0 ? STAGES - 1 : cur - 1);
     const uint16_t* kst = smem + cur * L::kStage;
     // Blocks wholly below the diagonal for every row of the wave skip the mask.
     if ((blk + 1) * kKeyBlk - 1 <= w_first)
