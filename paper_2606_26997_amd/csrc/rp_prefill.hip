@@ -183,7 +183,7 @@ __device__ inline void pf_copy(uint32_t lds, const uint16_t* base, uint32_t off)
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
                : "s"(lds), "v"(off), "s"(base)
-               : "memory");
+               : "m0", "memory");
 }
 // Waits until at most N of the wave's copies are in flight (and its LDS reads
 // are done), then for the workgroup's other waves.
