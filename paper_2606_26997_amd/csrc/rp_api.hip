@@ -1,6 +1,7 @@
 // C-ABI entry points: argument validation, workspace layout and kernel
 // launches on the caller's stream. No device allocation and no host sync on
 // the hot path; rp_validate_layout is the one test utility that does both.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -204,22 +205,34 @@ rp::PlanView plan_view(void* ws, const WsLayout& w) {
 // Whether rp_group_decode_attn runs as one launch, a workgroup per (sequence,
 // kv-head), instead of plan, parts and combine. Its seven shares of a
 // sequence's pages (as many as the tables hold) take steps of 8 KiB of K and V
-// one after the other, about 0.85 us each, where the three launches take 13-18
-// us however short the batch; with four or more query rows per kv-head those
-// take longer (a group's rows need several passes over its prefix). Measured,
-// three launches against one, in us (Hq / Hkv, sequences x kv-heads x pages):
-//   2: 4 x 2 x 12 13.2, 8.2; 16 x 8 x 64 19.3, 15.0; 16 x 8 x 126 21.1, 24.8;
-//      2 x 8 x 128 18.1, 20.7; 64 x 8 x 32 22.6, 16.3
-//   4: 16 x 2 x 126 27.9, 23.9;  8: 64 x 2 x 63 49.8, 16.3; 8 x 4 x 129 44.0, 24.0
-// so the line lies at 10 and 20 steps. It reads a group's prefix once per
-// member, so the batch's tables may span at most 128 MiB of K and V; the plan
-// that it leaves in the workspace is made by one wave (at most 64 sequences).
+// one after the other; the three launches have more waves to share the pages
+// but a longer chain of round trips, take one pass over a group's prefix for
+// every 16 of its query rows, and slow down sooner as the batch's K and V grow.
+// The line lies where the two are equal. Measured, three launches against one,
+// in us at 4, 8, 10 and 16 steps (Hq / Hkv and d of the layer, sequences x
+// kv-heads; 20-50% of the pages prefix):
+//   2, 128 bf16, 1 x 1:  13.3 8.8, 14.6 12.9, 14.2 14.3, 15.2 20.9
+//                16 x 8: 18.8 10.1, 19.8 14.8, 20.6 17.6, 25.0 24.8
+//   2, 64 bf16,  1 x 1:  10.9 8.3, 11.6 11.9, 11.8 13.7, 12.3 19.6
+//   2, 128 fp8,  1 x 1:  14.4 10.3, 14.8 15.0, 14.8 17.2, 16.0 23.7
+//   2, 64 fp8,   1 x 1:  12.6 11.2, 13.2 17.9, 13.6 20.9, 14.2 30.4
+//                16 x 8: 16.0 12.9, 20.3 19.7, 22.0 23.4, 28.7 33.5
+//   4, 64 fp8,   16 x 2 (2 groups): 18.9 12.1, 19.5 18.9, 20.3 22.2, 21.6 32.3
+//   8, 128 bf16, 16 x 2 (2 groups): 37.5 9.7, 41.1 14.2, 42.4 16.6, 42.9 23.6
+// The batch's tables may span at most 128 MiB of K and V, since each member
+// reads its group's prefix for itself, and the plan that the one launch leaves
+// in the workspace is made by one wave (at most 64 sequences).
 bool small_batch(const Shape& sh) {
   const long long page_bytes = 2ll * rp::kPage * sh.D * (sh.fp8 ? 1 : 2);  // K and V of a (page, kv-head)
-  const long long pages = (long long)sh.max_pp + sh.max_rp, step_pages = 8192 / page_bytes;
-  const int steps = sh.nrep >= 4 ? 20 : 10;
-  return sh.S <= rp::kSmallPlanMaxSeqs && pages <= (rp::kSmallWaves - 1) * steps * step_pages &&
-         pages * sh.S * sh.Hkv * page_bytes <= (128ll << 20);
+  const long long pages = (long long)sh.max_pp + sh.max_rp, per_step = (rp::kSmallWaves - 1) * (8192 / page_bytes);
+  const long long steps = (pages + per_step - 1) / per_step, kv_bytes = pages * sh.S * sh.Hkv * page_bytes;
+  if (sh.S > rp::kSmallPlanMaxSeqs || steps > (sh.nrep >= 4 ? 20 : 10) || kv_bytes > (128ll << 20)) return false;
+  const bool wide = sh.D == 128;
+  const int passes = rp::cdiv(sh.nrep * rp::cdiv(sh.S, sh.G), 16);  // over the prefix of a group of average size
+  const double one_us = (double)steps * (!sh.fp8 ? 1.0 : wide ? 1.15 : 1.55);
+  const double three_us = (!wide ? 8.0 : sh.fp8 ? 9.0 : 10.0) + 0.05 * (double)kv_bytes / (1 << 20) +
+                          (passes - 1) * std::min(sh.max_pp, rp::kPrefixChunkPages) * (wide ? 0.45 : 0.25);
+  return one_us <= three_us;  // both beyond what the shortest call takes
 }
 
 rp_status prepare(const rp_paged_kv* kv, const rp_group_layout* l, void* ws, size_t ws_bytes, Shape* sh,

@@ -140,9 +140,10 @@ def test_fp8_unit_order_covers_every_unit(hkv, lens):
 
 
 # (Hq, Hkv, d, dtype, groups' prefix lengths, group of each sequence, response lengths): batches on both
-# sides of the line between one launch and three (64 sequences; 70 pages in the tables at 128-wide bf16
-# heads, 140 at half the bytes, twice that from four query rows per kv-head), pieces that end with the
-# prefix, with a page and inside a step, empty prefixes and responses.
+# sides of the lines between one launch and three (64 sequences; the steps of 7 x 8 KiB of K and V that the
+# tables take, at most 10, or 20 from four query rows per kv-head, and fewer for fp8 and 64-wide heads unless
+# a group's rows need several passes over its prefix), pieces that end with the prefix, with a page and inside
+# a step, empty prefixes and responses.
 SMALL = [
     (4, 2, 64, "bf16", [128], [0] * 4, [32, 43, 54, 64]),
     (16, 8, 128, "bf16", [17, 0, 130], [0, 0, 1, 1, 2], [0, 1, 0, 16, 300]),
@@ -150,9 +151,15 @@ SMALL = [
     (8, 8, 128, "bf16", [560, 1], [0, 1, 0], [559, 561, 3]),          # 71: three launches
     (6, 3, 64, "fp8", [40, 1200], [0, 1, 1, 0], [1000, 7, 33, 0]),    # 138 pages of 1 KiB
     (16, 2, 128, "fp8", [300, 90], [0] * 5 + [1] * 3, [5, 900, 64, 63, 65, 0, 129, 800]),
-    (8, 1, 128, "bf16", [1000], [0, 0], [1200, 1]),                   # 138 of at most 140 pages
+    (8, 1, 128, "bf16", [1000], [0, 0], [1200, 1]),                   # 20 steps, one pass: three launches
     (4, 2, 64, "bf16", [20, 33], [i % 2 for i in range(64)], [3 * i for i in range(64)]),
     (4, 2, 64, "bf16", [20, 33], [i % 2 for i in range(65)], [3 * i for i in range(65)]),  # three launches
+    (8, 1, 128, "bf16", [1000], [0] * 8, [1200, 1, 0, 16, 700, 33, 15, 64]),  # 20 steps, four passes: one launch
+    (4, 2, 64, "fp8", [480, 3], [0, 0], [1740, 5]),                   # 139 pages of 1 KiB, 5 steps: one launch
+    (4, 2, 64, "fp8", [480, 3], [0, 0], [1800, 5]),                   # 143 pages, 6 steps: three
+    (16, 2, 64, "fp8", [300, 90], [0] * 5 + [1] * 3, [5, 2400, 64, 63, 65, 0, 129, 800]),  # 7 steps, two passes: one
+    (4, 2, 64, "bf16", [480, 3], [0, 0], [1290, 5]),                  # 111 pages of 2 KiB, 8 steps: one launch
+    (4, 2, 64, "bf16", [480, 3], [0, 0], [1330, 5]),                  # 114 pages, 9 steps: three
 ]
 
 
