@@ -69,19 +69,13 @@ __device__ inline double bf16_word_f64(const uint32_t* w, int p) {
   return (double)(p & 1 ? bf16_hi(w[p >> 1]) : bf16_lo(w[p >> 1]));
 }
 
-// Where the sequence's new token goes: first (page, kv-head) block of its page
-// (-1: nowhere) and row in it.
-struct AppendAt {
-  long long slot;
-  int row;
-};
-
-// One head slot; returns the requantisation that its append leaves to do.
+// One head slot; returns the requantisation that its append leaves to do. For
+// fp8 pools `page_blk` is the first (page, kv-head) block of the new token's
+// page (-1: no slot for it) and `old_scale` the head's scale there.
 template <int D, bool FP8>
-__device__ inline RequantJob prep_slot(const QkPrepArgs& a, int s, int kind, int head, int l16, const AppendAt& at,
-                                 float old_scale,
-                                 const uint32_t (&x1)[D / 64], const uint32_t (&x2)[D / 64],
-                                 const double (*s_tab)[4][D / 2]) {
+__device__ inline RequantJob prep_slot(const QkPrepArgs& a, int s, int kind, int head, int l16, int L,
+                                       long long page_blk, float old_scale, const uint32_t (&x1)[D / 64],
+                                       const uint32_t (&x2)[D / 64], const double (*s_tab)[4][D / 2]) {
   constexpr int NP = D / 32;   // pairs per lane
   constexpr int W = NP / 2;    // 32-bit words per lane and half row
   constexpr int HALF = D / 2;
@@ -151,14 +145,17 @@ __device__ inline RequantJob prep_slot(const QkPrepArgs& a, int s, int kind, int
   }
 
   // Append of k (kind 1) or v (kind 2) at response slot L.
-  if (at.slot < 0) return RequantJob{};  // no slot for the new token
-  const size_t blk = ((size_t)at.slot + head) * kPage * D;  // in elements
   if constexpr (!FP8) {
-    uint16_t* dst = static_cast<uint16_t*>(kind == 1 ? a.k_pages : a.v_pages) + blk + (size_t)at.row * D;
+    if (L < 0 || L >= a.max_resp_pages * kPage) return RequantJob{};  // no slot for the new token
+    const int page = clamp_page(a.resp_block_table[(size_t)s * a.max_resp_pages + L / kPage], a.num_pages);
+    const size_t blk = ((size_t)page * Hkv + head) * kPage * D;  // in elements
+    uint16_t* dst = static_cast<uint16_t*>(kind == 1 ? a.k_pages : a.v_pages) + blk + (size_t)(L % kPage) * D;
     store_words<W>(dst, c1, o1);
     store_words<W>(dst, c2, o2);
     return RequantJob{};
   } else {
+    if (page_blk < 0) return RequantJob{};
+    const size_t blk = ((size_t)page_blk + head) * kPage * D;  // in bytes
     float xf[2 * NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -167,8 +164,8 @@ __device__ inline RequantJob prep_slot(const QkPrepArgs& a, int s, int kind, int
     }
     const int col[2] = {c1, c2};
     return append_fp8_row<D, kSlotLanes, NP>(static_cast<uint8_t*>(kind == 1 ? a.k_pages : a.v_pages) + blk,
-                                             (kind == 1 ? a.k_scale : a.v_scale) + at.slot + head, old_scale, at.row,
-                                             xf, col, l16 == 0);
+                                             (kind == 1 ? a.k_scale : a.v_scale) + page_blk + head, old_scale,
+                                             L % kPage, xf, col, l16 == 0);
   }
 }
 
@@ -207,19 +204,19 @@ __device__ __forceinline__ void prep_block(const QkPrepArgs& a, int bid, PrepTab
       load_words<W>(src, c2, x2[k]);
     }
   }
-  // The append's page, and the scales it starts from, are loaded here too, so
-  // that their round trips pass behind the tables.
-  AppendAt at = {-1, 0};
+  // An fp8 append's page, and the scales it starts from, are loaded here too,
+  // so that their round trips pass behind the tables. A bf16 append has one
+  // round trip less and none of its waits may come before the tables (the
+  // page loaded here: 1024 blocks and more 2-3% slower at d 128).
+  long long page_blk = -1;
   float old_scale[SPL];
-  if (L >= 0 && L < a.max_resp_pages * kPage) {
-    at.slot = (long long)clamp_page(a.resp_block_table[(size_t)s * a.max_resp_pages + L / kPage], a.num_pages) * Hkv;
-    at.row = L % kPage;
-  }
+  if (FP8 && L >= 0 && L < a.max_resp_pages * kPage)
+    page_blk = (long long)clamp_page(a.resp_block_table[(size_t)s * a.max_resp_pages + L / kPage], a.num_pages) * Hkv;
 #pragma unroll
   for (int k = 0; k < SPL; ++k) {
     old_scale[k] = 1.f;
-    if (FP8 && at.slot >= 0 && (kind[k] == 1 || kind[k] == 2))
-      old_scale[k] = (kind[k] == 1 ? a.k_scale : a.v_scale)[at.slot + head[k]];
+    if (FP8 && page_blk >= 0 && (kind[k] == 1 || kind[k] == 2))
+      old_scale[k] = (kind[k] == 1 ? a.k_scale : a.v_scale)[page_blk + head[k]];
   }
   if (t < HALF) {
     const double pos = (double)a.prefix_lens[g] + (double)L;
@@ -240,7 +237,7 @@ __device__ __forceinline__ void prep_block(const QkPrepArgs& a, int bid, PrepTab
 #pragma unroll
   for (int k = 0; k < SPL; ++k) {
     RequantJob job = {};
-    if (kind[k] < 3) job = prep_slot<D, FP8>(a, s, kind[k], head[k], l16, at, old_scale[k], x1[k], x2[k], s_tab);
+    if (kind[k] < 3) job = prep_slot<D, FP8>(a, s, kind[k], head[k], l16, L, page_blk, old_scale[k], x1[k], x2[k], s_tab);
     if constexpr (FP8) requantise_fp8_rows<D>(job, l16 == 0, t & 63);
   }
 }
