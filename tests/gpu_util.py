@@ -28,11 +28,21 @@ def to_host_out(batch):
     return out, lse
 
 
-def run_hip(wl, batch=None):
+def run_hip(wl, batch=None, staged=False):
+    """The batch's step in one call, or, `staged`, its append, plan, partial attention and combine (which
+    small batches, whose one call is a single launch, reach only this way)."""
     import paper_2606_26997_amd as rp
     if batch is None:
         batch = rp.DeviceBatch.from_workload(wl)
-    batch.step()
+    if staged:
+        if batch.append:
+            batch.kv_append()
+        batch.workspace.fill_(0xFF)  # NaN partials: one that is not written shows
+        batch.plan()
+        batch.attn_parts()
+        batch.combine_parts()
+    else:
+        batch.step()
     out, lse = to_host_out(batch)
     return batch, out, lse
 

@@ -16,6 +16,10 @@ from workloads import CONFIGS, make_config_workload, make_workload
 
 pytestmark = pytest.mark.gpu
 
+# Small batches take one launch in the one call; their plan, prefix and response units and combine run only
+# in the staged form.
+both_forms = pytest.mark.parametrize("staged", [False, True], ids=["one-call", "staged"])
+
 
 def _say(msg):
     print(f"[case] {msg}", flush=True)
@@ -49,16 +53,25 @@ RAGGED = [
     # Lengths at the edges of 64-page multiples (32-page pieces: the batch is small).
     ("piece-edges-long", 4, 2, 64, [0, 0, 0, 1, 1, 1, 1], [100, 16],
      [4090, 4096, 4097, 8191, 8192, 1000, 12000], "bf16"),
+    # Several passes of 16 query rows over a prefix of more than one 16-page chunk with a ragged end.
+    ("passes-nrep4-d64", 32, 8, 64, [0] * 9 + [1] * 2, [300, 17], [0, 5, 16, 33, 64, 100, 7, 250, 31, 15, 40], "bf16"),
+    ("passes-nrep4-d128", 8, 2, 128, [0] * 9 + [1] * 5, [515, 256], [0, 5, 16, 33, 64, 100, 7, 250, 31, 15, 40, 1, 90, 3],
+     "bf16"),
+    ("passes-nrep8-d128", 16, 2, 128, [0] * 7 + [1] * 3, [273, 300], [0, 5, 16, 33, 64, 100, 7, 250, 31, 15], "bf16"),
+    ("passes-nrep8-d64", 8, 1, 64, [0] * 5, [301], [40, 0, 16, 64, 300], "bf16"),
+    ("passes-nrep8-fp8", 16, 2, 128, [0] * 5 + [1], [270, 33], [40, 0, 16, 64, 300, 9], "fp8"),
+    ("passes-nrep4-fp8-d64", 16, 4, 64, [0] * 9, [330], [40, 0, 16, 64, 300, 9, 65, 1, 128], "fp8"),
 ]
 
 
+@both_forms
 @pytest.mark.parametrize("case", RAGGED, ids=[c[0] for c in RAGGED])
-def test_ragged_shapes(case):
+def test_ragged_shapes(case, staged):
     name, Hq, Hkv, d, s2g, P, L, dt = case
     _say(name)
     wl = make_workload(num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, seq_to_group=s2g,
                        prefix_lens=P, resp_lens=L, seed=zlib.crc32(name.encode()) % 1000, kv_dtype=dt)
-    _, out, lse = run_hip(wl)
+    _, out, lse = run_hip(wl, staged=staged)
     ref_out, ref_lse, _ = run_oracle(wl)
     compare(out, lse, ref_out, ref_lse, dt, name)
 
@@ -91,8 +104,9 @@ def test_more_sequences_than_the_planner_caches():
     compare(out, lse, ref_out, ref_lse, "bf16", "8500-seqs")
 
 
+@both_forms
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8"])
-def test_append_bytes_match_oracle_then_attention(kv_dtype):
+def test_append_bytes_match_oracle_then_attention(kv_dtype, staged):
     _say(f"append {kv_dtype}")
     rng = np.random.default_rng(11)
     S = 40
@@ -103,7 +117,7 @@ def test_append_bytes_match_oracle_then_attention(kv_dtype):
                        kv_dtype=kv_dtype)
     if kv_dtype == "fp8":  # make some appends grow the page scale (requantise path)
         wl.k_new[::3] = bf16_bits(oracle.bf16_to_f32(wl.k_new[::3]) * np.float32(40.0))
-    batch, out, lse = run_hip(wl)
+    batch, out, lse = run_hip(wl, staged=staged)
     ref_out, ref_lse, pool = run_oracle(wl)
     kp, vp, ks, vs = pool
     torch.cuda.synchronize()
@@ -117,8 +131,7 @@ def test_append_bytes_match_oracle_then_attention(kv_dtype):
         assert np.array_equal(batch.v_pages.view(torch.int16).cpu().numpy().view(np.uint16), vp)
     compare(out, lse, ref_out, ref_lse, kv_dtype, f"append-{kv_dtype}")
     # The append is idempotent: a second step changes nothing.
-    batch.step()
-    out2, lse2 = to_host_out(batch)
+    _, out2, lse2 = run_hip(wl, batch, staged=staged)
     assert np.array_equal(out, out2) and np.array_equal(lse, lse2)
 
 
@@ -152,7 +165,8 @@ def test_fp8_append_nan_element_takes_the_saturated_code():
     assert np.array_equal(b.k_scale.cpu().numpy(), ks)
 
 
-def test_zero_query_gives_log_key_count():
+@both_forms
+def test_zero_query_gives_log_key_count(staged):
     """q = 0: lse = ln N exactly up to fp32, which pins the number of keys read."""
     _say("q=0 key count")
     rng = np.random.default_rng(3)
@@ -160,7 +174,7 @@ def test_zero_query_gives_log_key_count():
     wl = make_workload(num_q_heads=16, num_kv_heads=8, head_dim=128, seq_to_group=np.arange(S) // 8,
                        prefix_lens=[100, 255, 17], resp_lens=rng.integers(0, 3000, size=S), seed=1)
     wl.q[:] = 0
-    _, out, lse = run_hip(wl)
+    _, out, lse = run_hip(wl, staged=staged)
     N = np.array([wl.prefix_lens[wl.seq_to_group[s]] + wl.resp_lens[s] for s in range(S)])
     np.testing.assert_allclose(lse, np.log(N)[:, None].repeat(16, 1), rtol=0, atol=2e-5)
     ref_out, ref_lse, _ = run_oracle(wl)
@@ -201,7 +215,8 @@ def test_dominant_key_sweep_every_slot():
     compare(out, lse, ref_out, ref_lse, "bf16", "dominant-key")
 
 
-def test_physical_page_permutation_bitwise_and_determinism():
+@both_forms
+def test_physical_page_permutation_bitwise_and_determinism(staged):
     _say("page permutation")
     rng = np.random.default_rng(8)
     pk, pv, rk, rv, s2g, q = random_dense(rng, S=12, G=3, Hq=16, Hkv=8, d=128,
@@ -209,15 +224,15 @@ def test_physical_page_permutation_bitwise_and_determinism():
                                           resp_lens=list(rng.integers(0, 400, size=12)))
     wl1 = paged_from_dense(pk, pv, rk, rv, s2g, q, num_kv_heads=8, seed=1)
     wl2 = paged_from_dense(pk, pv, rk, rv, s2g, q, num_kv_heads=8, seed=2, pad_pages=7)
-    b1, o1, l1 = run_hip(wl1)
-    _, o2, l2 = run_hip(wl2)
+    b1, o1, l1 = run_hip(wl1, staged=staged)
+    _, o2, l2 = run_hip(wl2, staged=staged)
     assert np.array_equal(o1, o2) and np.array_equal(l1, l2)
-    b1.step()
-    o3, l3 = to_host_out(b1)
+    _, o3, l3 = run_hip(wl1, b1, staged=staged)
     assert np.array_equal(o1, o3) and np.array_equal(l1, l3)
 
 
-def test_shared_prefix_equals_duplicated_prefix_on_gpu():
+@both_forms
+def test_shared_prefix_equals_duplicated_prefix_on_gpu(staged):
     _say("shared vs duplicated prefix")
     rng = np.random.default_rng(12)
     S, G = 16, 2
@@ -229,14 +244,16 @@ def test_shared_prefix_equals_duplicated_prefix_on_gpu():
     dup = paged_from_dense(empty, empty, [np.concatenate([pk[s2g[s]], rk[s]]) for s in range(S)],
                            [np.concatenate([pv[s2g[s]], rv[s]]) for s in range(S)], np.arange(S), q,
                            num_kv_heads=8, seed=4)
-    _, o1, l1 = run_hip(shared)
-    _, o2, l2 = run_hip(dup)
-    # Different split points and MFMA vs VALU arithmetic: equal within rounding.
+    _, o1, l1 = run_hip(shared, staged=staged)
+    _, o2, l2 = run_hip(dup, staged=staged)
+    # Staged, shared keys go through the prefix units (probabilities rounded to bf16) and duplicated ones
+    # through the response units; other split points in either form: equal within rounding.
     assert np.abs(o1 - o2).max() <= 1e-2
     assert np.abs(l1 - l2).max() <= 1e-4
 
 
-def test_logical_key_order_permutation_within_tolerance():
+@both_forms
+def test_logical_key_order_permutation_within_tolerance(staged):
     # Attention over a set of keys does not depend on their order: the same
     # keys in another logical order (prefix and response rows shuffled, so
     # pieces, chunks and page boundaries all change) give the same result up
@@ -252,15 +269,16 @@ def test_logical_key_order_permutation_within_tolerance():
     wl2 = paged_from_dense([x[i] for x, i in zip(pk, perm_p)], [x[i] for x, i in zip(pv, perm_p)],
                            [x[i] for x, i in zip(rk, perm_r)], [x[i] for x, i in zip(rv, perm_r)],
                            s2g, q, num_kv_heads=8, seed=6)
-    _, o1, l1 = run_hip(wl1)
-    _, o2, l2 = run_hip(wl2)
+    _, o1, l1 = run_hip(wl1, staged=staged)
+    _, o2, l2 = run_hip(wl2, staged=staged)
     assert np.abs(o1 - o2).max() <= 1e-2
     assert np.abs(l1 - l2).max() <= 1e-4
     ref_out, ref_lse = oracle.attention_for_workload(wl1)
     compare(o2, l2, ref_out, ref_lse, "bf16", "permuted keys")
 
 
-def test_gqa_mapping_value_in_one_kv_head():
+@both_forms
+def test_gqa_mapping_value_in_one_kv_head(staged):
     # V nonzero in kv-head 3 only: exactly query heads 6 and 7 (n_rep = 2,
     # q-head j reads kv-head j // 2) have a nonzero output; every other
     # head's output is exactly zero.
@@ -271,7 +289,7 @@ def test_gqa_mapping_value_in_one_kv_head():
     pk, pv, rk, rv, s2g, q = random_dense(rng, S=S, G=G, Hq=16, Hkv=8, d=128, prefix_lens=P, resp_lens=L)
     keep = lambda x: np.where((np.arange(8) == h)[None, :, None], x, np.uint16(0))
     wl = paged_from_dense(pk, [keep(x) for x in pv], rk, [keep(x) for x in rv], s2g, q, num_kv_heads=8, seed=7)
-    _, out, lse = run_hip(wl)
+    _, out, lse = run_hip(wl, staged=staged)
     others = [j for j in range(16) if j // 2 != h]
     assert np.all(out[:, others] == 0)
     assert np.all(np.abs(out[:, [2 * h, 2 * h + 1]]).max(axis=2) > 0)
@@ -279,7 +297,8 @@ def test_gqa_mapping_value_in_one_kv_head():
     compare(out, lse, ref_out, ref_lse, "bf16", "one kv-head")
 
 
-def test_fp8_all_codes_decode_like_the_oracle():
+@both_forms
+def test_fp8_all_codes_decode_like_the_oracle(staged):
     """A single key: out = decoded V codes * v_scale exactly (bf16 holds every e4m3 value)."""
     _say("fp8 256 codes")
     codes = np.arange(256, dtype=np.uint8)
@@ -292,7 +311,7 @@ def test_fp8_all_codes_decode_like_the_oracle():
         wl.v_pages[page, 0, 0, :] = codes[s * 128:(s + 1) * 128]
         wl.v_scale[page, 0] = np.float32(1.0)
         wl.k_scale[page, 0] = np.float32(0.5)
-    _, out, lse = run_hip(wl)
+    _, out, lse = run_hip(wl, staged=staged)
     ref_out, ref_lse, _ = run_oracle(wl)
     want = oracle.e4m3_to_f64(codes).reshape(2, 1, 128)
     assert np.array_equal(out[:, 0:1, :], want) and np.array_equal(out[:, 1:2, :], want)
