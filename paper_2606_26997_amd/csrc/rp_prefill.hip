@@ -248,19 +248,20 @@ __device__ inline bool pf_unit(int b, int NP, int max_blocks, int stride, int* p
 }
 
 // The one-launch prefill writes a prompt's K/V rows into the group's prefix
-// pages once a workgroup's attention is done: the rows are then in this XCD's
-// L2, and no register or wait of the key loop is spent on them. bf16 rows are
-// written by the workgroup whose query rows hold the token (exactly one), fp8
-// pages, whose scale needs all their rows, by the one that holds the page's
-// first token. Rows past the prompt's end are not written, as in the
-// page-write kernel. (fp8, 32 prompts of U[64, 512]: a page-write launch before
-// the attention 69 us in all, together 55.)
+// pages once a workgroup's attention is done: no register or wait of the key
+// loop is spent on them. bf16 rows are written by the workgroup whose query
+// rows hold the token (exactly one), fp8 pages, whose scale needs all their
+// rows, by the one that holds the page's first token. Rows past the prompt's
+// end are not written, as in the page-write kernel. (fp8, 32 prompts of
+// U[64, 512]: a page-write launch before the attention 69 us in all, together
+// 55.)
 //
-// Short prompts run every instruction once, so what is fetched counts: the bf16
-// rows go in a loop that is not unrolled and ends with the prompt (4 prompts of
-// U[16, 64] at Hq 8, Hkv 8: unrolled 6.25 us, this way 5.80; 32 at Hq 16 9.0,
-// 8.6). Page ids loaded ahead of the key loop and rows written from LDS were no
-// faster.
+// bf16 rows come from LDS with one row tile per wave, where the last two key
+// blocks hold them all, and from L2 with two (32 prompts of U[128, 256] at Hq 8,
+// Hkv 8 from L2 19.2 us, from LDS 17.9; at 32 kv-heads 81.8, 74.3). Short
+// prompts run every instruction once, so what is fetched counts: the loops are
+// not unrolled and end with the prompt (4 prompts of U[16, 64] at Hq 8, Hkv 8:
+// unrolled 6.25 us, rolled 5.80).
 template <int D, int TPB>
 __device__ inline void pf_write_pages_fp8(const PrefillArgs& a, int g, int h, int T0, int last, int wave, int lane,
                                           const uint16_t* kbase, const uint16_t* vbase, uint32_t pitch) {
@@ -279,6 +280,27 @@ __device__ inline void pf_write_pages_fp8(const PrefillArgs& a, int g, int h, in
     head[0].store(static_cast<uint8_t*>(v_only ? a.v_pages : a.k_pages) + dst, (v_only ? a.v_scale : a.k_scale) + slot,
                   rows, lane);
     if constexpr (SPLIT == 1) head[1].store(static_cast<uint8_t*>(a.v_pages) + dst, a.v_scale + slot, rows, lane);
+  }
+}
+
+// From LDS: `last_blk` is the stage of key block `blk`, the workgroup's last,
+// `prev_blk` that of the block before.
+template <int D, int TPB>
+__device__ inline void pf_write_staged(const PrefillArgs& a, int g, int h, int T0, int last, int t, int blk,
+                                       const uint16_t* last_blk, const uint16_t* prev_blk) {
+  using L = PfSmem<D>;
+  static_assert(TPB <= 2 * kKeyBlk, "the workgroup's rows are staged");
+  const int* pbt = a.prefix_block_table + (size_t)g * a.max_prefix_pages;
+  const int n = min(TPB, last + 1 - T0) * (D / 8);
+#pragma unroll 1
+  for (int c = t; c < n; c += kPfThreads) {
+    const int col = (c % (D / 8)) * 8, u = T0 + c / (D / 8);
+    const uint16_t* src = (u / kKeyBlk == blk ? last_blk : prev_blk) + L::row(u % kKeyBlk) + col;
+    const int page = clamp_page(pbt[u / kPage], a.num_pages);
+    const size_t dst = (((size_t)page * a.num_kv_heads + h) * kPage + (u % kPage)) * D + col;
+    *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(a.k_pages) + dst) = *reinterpret_cast<const u32x4_t*>(src);
+    *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(a.v_pages) + dst) =
+        *reinterpret_cast<const u32x4_t*>(src + L::kElems);
   }
 }
 
@@ -511,7 +533,10 @@ void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride) {
     cur = cur == STAGES - 1 ? 0 : cur + 1;
   }
 
-  if constexpr (WP == kPagesBf16) pf_write_pages<D, TPB>(a, g, h, T0, last, t, kbase, vbase, (uint32_t)kpitch);
+  if constexpr (WP == kPagesBf16 && RT == 1)  // `cur` is past the last block's stage
+    pf_write_staged<D, TPB>(a, g, h, T0, last, t, nblk - 1, smem + (1 - cur) * L::kStage, smem + cur * L::kStage);
+  else if constexpr (WP == kPagesBf16)
+    pf_write_pages<D, TPB>(a, g, h, T0, last, t, kbase, vbase, (uint32_t)kpitch);
 
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
