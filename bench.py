@@ -363,25 +363,17 @@ def prefill_bench(args):
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) / args.steps * 1e3
     attn_us = float(np.mean([a.elapsed_time(c) for a, c in ev])) * 1e3
-    # The timed call's bytes: q, k, v read, out and lse written, and the pages
-    # written (bf16: by the attention launch itself; fp8: by the page-write
-    # kernel that runs first, which reads k and v once more and writes the
-    # codes and the per-(page, kv-head) scales).
-    attn_bytes = T * (Hq + 2 * Hkv + Hq) * d * 2 + T * Hq * 4 + T * Hkv * d * 2 * eb
-    if eb == 1:
-        attn_bytes += T * Hkv * d * 2 * 2 + int(((P64 + 15) // 16).sum()) * Hkv * 8
     # Below the bf16 ridge (about 310 flop/B) the kernel is priced against HBM
     # bandwidth, above it against the dense bf16 MFMA peak.
-    gbps_attn = attn_bytes / (attn_us * 1e-6) / 1e9
+    gbps_attn = nbytes / (attn_us * 1e-6) / 1e9
     tflops_attn = flops / (attn_us * 1e-6) / 1e12
-    kname = "prefill_attn_kernel" if eb == 2 else "prefill_kv_write_kernel + prefill_attn_kernel"
-    if flops / attn_bytes < 310:
-        roof = {"kernel": kname, "bound": "hbm", "achieved": round(gbps_attn, 1),
+    if flops / nbytes < 310:
+        roof = {"kernel": "prefill_attn_kernel", "bound": "hbm", "achieved": round(gbps_attn, 1),
                 "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(gbps_attn / HBM_PEAK_GBPS, 4)}
     else:
-        roof = {"kernel": kname, "bound": "mfma", "achieved": round(tflops_attn, 1),
+        roof = {"kernel": "prefill_attn_kernel", "bound": "mfma", "achieved": round(tflops_attn, 1),
                 "peak": 2500.0, "unit": "TFLOP/s", "frac": round(tflops_attn / 2500.0, 4)}
-    roof.update({"traffic": None, "algorithmic_bytes_per_launch": int(attn_bytes), "flops_per_launch": flops,
+    roof.update({"traffic": None, "algorithmic_bytes_per_launch": int(nbytes), "flops_per_launch": flops,
                  "mfma_frac": round(tflops_attn / 2500.0, 4)})
     line = {
         "metric": "shared-prefix prefill: prompt tokens/s and achieved HBM GB/s (one prompt per group)",
