@@ -193,5 +193,5 @@ class PrefillBatch:
         self.attention(stream)
 
     def prefill(self, stream=None):
-        """The same results as ``step`` through rp_prefill (one launch for a bf16 pool)."""
+        """The same results as ``step`` through rp_prefill, in one launch."""
         B.prefill(self.kv, self.layout, self.q, self.k, self.v, self.softmax_scale, self.out, self.lse, stream)

@@ -18,9 +18,8 @@ HOST_SOURCES = ["rp_sched.cpp"]
 ARCH = "gfx950"
 
 # Packed-fp32 VALU instructions are disabled for all device code. MFMA
-# accumulators are kept in ordinary VGPRs so that the prefix path of the
-# partial-attention kernel does not add accumulation registers on top of the
-# response path's budget.
+# accumulators are kept in ordinary VGPRs: the attention kernels' softmax works
+# on them between products.
 HIPCC_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                "-mllvm", "-amdgpu-mfma-vgpr-form",

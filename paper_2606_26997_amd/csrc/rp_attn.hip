@@ -391,10 +391,10 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
 // One group-prefix unit: kv-head h of (group, chunk of prefix pages), for all
 // query rows of the group's live members, 16 rows per pass. A group with more
 // than 16 query rows reads the chunk again for each further pass; the chunk
-// (a few tens of KiB) is then still in this XCD's L2, its V too, since prefix
-// units load it without the non-temporal hint (64 rows a group, Hq 32, Hkv 4,
-// 256 sequences: 395.9 us a step with the hint, 392.2 without; 16 rows 367 both
-// ways).
+// (128 KiB of K and V with 128-wide bf16 heads, half of that with 64-wide or fp8
+// ones) is then mostly in this XCD's L2, its V too, since prefix units load it
+// without the non-temporal hint (64 rows a group, Hq 32, Hkv 4, 256 sequences:
+// 395.9 us a step with the hint, 392.2 without; 16 rows 367 both ways).
 template <int D, int NREP, bool FP8>
 __device__ void prefix_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
   const int2 it = a.view.prefix_items[item];
@@ -487,8 +487,8 @@ void attn_parts_kernel(const AttnArgs a) {
       // Workgroups are dealt to the 8 XCDs in turn, so eight items interleaved
       // put all kv-heads of an item on one XCD: the scales of a page's heads
       // share a cache line, which its L2 then fetches once (256 sequences of
-      // 8192-32768 tokens: 1748 -> 1675 us a step). bf16 pools have no such
-      // line and are 0.1-0.5% slower this way.
+      // 8192-32768 tokens: 1677 -> 1662 us a step, d 64 905 -> 887). bf16
+      // pools have no such line and are 0.1-0.5% slower this way.
       const int row = resp / (8 * Hkv), k = resp - row * (8 * Hkv);
       if ((row + 1) * (8 * Hkv) <= n_resp) {
         item = row * 8 + k % 8;
@@ -502,7 +502,11 @@ void attn_parts_kernel(const AttnArgs a) {
 // A small batch whole, in one launch: a workgroup per (sequence, kv-head)
 // splits the prefix and the response pages into at most kSmallWaves pieces, a
 // wave each, and merges their partials in LDS; each sequence reads its
-// group's prefix for itself (from L2 after the first). Block 0 makes the
+// group's prefix for itself. Both kinds of pages load V with the hint: prefix
+// pages without it are 1-7% faster where one large group shares a long prefix
+// (64 sequences of 900 + 200 tokens, 2 kv-heads: 17.4 -> 16.6 us), and 1-4%
+// slower where several groups of 16 have as much response (4 x 16 of 300 + 300,
+// 4 kv-heads 13.6 -> 14.0). Block 0 makes the
 // batch's plan, as the three-launch form leaves it in the workspace, and a
 // row's merged result becomes its first partial there (the others empty), so
 // that a combine on the workspace gives out and lse again. Bound by the chain of round trips and steps of one wave (4 sequences of 192 tokens, 2

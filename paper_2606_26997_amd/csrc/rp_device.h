@@ -59,7 +59,6 @@ constexpr int kSmallWaves = 8;
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 __host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -95,13 +94,6 @@ __device__ inline int clamp_part(int p, int max_parts) {
 __device__ inline float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// fp32 -> bf16 bits, round to nearest even (NaN kept quiet).
-__device__ inline uint32_t f32_to_bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0u;
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return u >> 16;
-}
 // Two fp32 values to packed bf16 (low half first), round to nearest even, by
 // gfx950's packed conversion (a NaN stays a NaN).
 __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
@@ -112,10 +104,7 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
 }
 
 // ---- OCP e4m3fn -----------------------------------------------------------
-// Decoding uses gfx950's conversion instructions, which implement OCP e4m3fn.
-__device__ inline float e4m3_to_f32(uint32_t code) {
-  return __builtin_amdgcn_cvt_f32_fp8((int)code, 0);
-}
+// Decoding is gfx950's conversion instructions, which implement OCP e4m3fn.
 
 // fp32 -> e4m3fn code, round to nearest even, saturating at +-448. A NaN
 // input (inf included among |x| >= 448) also takes the saturated code, with
@@ -368,7 +357,7 @@ __device__ inline void requantise_fp8_rows(const RequantJob& job, bool leader, i
   }
 }
 
-// MFMA tiles used by the group-prefix and prefill paths (fp32 accumulate).
+// MFMA tiles of the decode and prefill attention (fp32 accumulate).
 // With lane l = 16 q + r (r < 16):
 //   16x16x32 bf16: lane (r, q) supplies A[r][8q..8q+7] and B[8q..8q+7][r];
 //   16x16x16 bf16: lane (r, q) supplies A[r][4q..4q+3] and B[4q..4q+3][r];

@@ -161,7 +161,8 @@ constexpr int kKeyBlk = 32;
 // chunk of kRows rows. Row r lies in chunk r % kChunks, slot r / kChunks, and
 // chunks are 32 bytes more than 1 KiB apart, so that the eight rows of a
 // 16-byte K read and the four rows of a transposing V read lie in different
-// banks, at offsets that are immediates of the reads.
+// banks (no conflict cycles by the counters), at offsets that are immediates of
+// the reads.
 template <int D>
 struct PfSmem {
   static constexpr int kRows = 512 / D;                 // rows per chunk
@@ -558,7 +559,14 @@ void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride) {
 
 // Row tiles per wave: two when prompts average 384 tokens or more (each K/V
 // operand read from LDS serves two MFMAs), one otherwise (twice the
-// workgroups, which balances ragged short prompts better; measured).
+// workgroups, which balances ragged short prompts better). Measured, one tile
+// against two, in us at Hkv 8 (Hq, d, prompts):
+//   16, 128, 32 x U[192, 320]: 32.1, 36.0;  32 x U[300, 400]: 45.1, 49.4
+//   16, 128, 64 x 400: 121.5, 114.7;        32 x U[700, 900]: 168.9, 147.6
+//   64, 128, 32 x U[300, 400]: 164.8, 148.7;  32, 64, 64 x 400: 121.2, 103.5
+//   16, 128, 2 x 500: 12.5, 17.9;           1 x 1000: 19.8, 27.6
+// A grid that fills the chip more than once gains by two tiles from about 300
+// (many query heads) to 500 tokens (few) on, a smaller one at no length.
 template <int D, int NREP>
 hipError_t attn_launch(const PrefillArgs& a, hipStream_t st) {
   const long long NP = (long long)a.num_groups * a.num_kv_heads;
