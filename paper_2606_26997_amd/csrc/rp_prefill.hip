@@ -212,17 +212,29 @@ __device__ inline void pf_load(uint32_t stage, const uint16_t* kbase, const uint
 
 // Which (group, kv-head) pair and row block a workgroup takes. Workgroups are
 // dealt to the 8 XCDs round-robin, so with NP a multiple of 8 all row blocks
-// of a pair run on one XCD, and the order keeps few pairs at a time there:
-// kPfPairs of them, their row blocks interleaved, the last rows (which see the
-// most keys) first. Their keys then stay in the XCD's L2 (all pairs at once:
-// 1024-token prompts 239 us against 198, 2048-4096 tokens 366 against 320). An
-// XCD deals its workgroups to its shader engines in turn as well: an odd
-// number of pairs and an odd `stride` from one set of pairs to the next (one
-// idle workgroup where needed) keep a pair, or a row block, from falling to
-// one engine every time (4 pairs instead of 5 on ragged prompts of 300-1800
-// tokens: 317 us against 208). stride = 0: any NP, pairs dealt in turn, which
-// is also the order of small grids.
+// of a pair run on one XCD, and the order keeps few pairs at a time there: sets
+// of `per_set`, their row blocks interleaved, the last rows (which see the most
+// keys) first. Their keys then stay in the XCD's L2 (all pairs at once instead
+// of five: 1024-token prompts 239 us against 198, 2048-4096 tokens 366 against
+// 320). An XCD deals its workgroups to its shader engines in turn as well: an
+// odd number of slots in a set (one idle where its pairs are even) and an odd
+// `stride` from set to set keep a pair, or a row block, from falling to one
+// engine every time (4 pairs instead of 5 on ragged prompts of 300-1800 tokens:
+// 317 us against 208; last sets of 4 pairs, 9 prompts of 59-1127 tokens at Hq
+// 64, Hkv 8: 120 us without the idle slot, 90 with).
+// stride = 0: any NP, pairs dealt in turn, which is also the order of small
+// grids.
 constexpr int kPfPairs = 5;
+// Pairs per set: all of an XCD's at once where they are few and their K and V
+// fit the L2s together; the last set, which starts its longest rows when the
+// others run dry, is otherwise a large part of such a grid (Hkv 8, d 128, us,
+// sets of 5 against one: 9 prompts of 59-1127 tokens at Hq 32 59.5, 49.5; 6 of
+// 100-1500 64.1, 51.0; 8 of 512-1024 62.6, 53.4. 32 or 64 pairs: 32 of U[64,
+// 256] 30.8, 33.8; 64 of U[32, 128] 28.2, 29.3).
+constexpr int kPfFewPairs = 16;
+__host__ inline int pf_set_pairs(long long pairs, long long kv_bytes) {
+  return pairs <= kPfFewPairs && kv_bytes <= (24ll << 20) ? (int)pairs : kPfPairs;
+}
 // Grids up to this many workgroups start nearly all of them at once (four 128-
 // wide or six 64-wide workgroups with one row tile fit a compute unit): there
 // is little left to keep in L2, and the long row blocks of all pairs first
@@ -232,20 +244,23 @@ constexpr int kPfPairs = 5;
 //   16 / 8, 128, 32 x U[32, 128]; 1024:  13.2, 12.7;  16 x U[300, 400]; 1664: 27.3, 28.2
 //   16 / 8, 128, 64 x U[64, 256]; 4096:  41.6, 36.3;  64 / 8, 8 x U[512, 1024]; 4096: 112, 101
 //   16 / 8, 64, 32 x U[16, 64]; 512:     5.88, 6.29;  64 x U[32, 128]; 2048: 11.4, 12.0
-//   32 / 8, 64, 8 x U[512, 1024]; 2048:  37.5, 40.0;  64 / 8, the same; 4096: 66.1, 59.7
-__host__ inline constexpr long long pf_small_grid(int head_dim) { return 1024 * 128 / head_dim; }
-__host__ __device__ inline int pf_stride(int max_blocks) { return (kPfPairs * max_blocks) | 1; }
-__device__ inline bool pf_unit(int b, int NP, int max_blocks, int stride, int* pair, int* rb) {
+// and against one set of few pairs:
+//   32 / 8, 128, 4 x 600; 608:           24.4, 25.9;  64, 4 x U[1000, 2000]; 2016: 63.5, 52.3
+//   8 / 8, 128, 12 x U[59, 1127]; 864:   34.5, 37.2;  16 / 8, 64, 8 x U[100, 1500]; 1536: 40.4, 35.2
+__host__ inline long long pf_small_grid(long long pairs, int head_dim) {
+  return pairs <= kPfFewPairs ? 1024 : 1024 * 128 / head_dim;
+}
+__device__ inline bool pf_unit(int b, int NP, int max_blocks, int stride, int per_set, int* pair, int* rb) {
   if (stride == 0) {
     *pair = b % NP;
     *rb = max_blocks - 1 - b / NP;
     return true;
   }
   const int i = b / 8, set = i / stride, r = i - set * stride;
-  const int m = min(kPfPairs, NP / 8 - set * kPfPairs);  // pairs of this set
-  *rb = max_blocks - 1 - r / m;
-  *pair = (set * kPfPairs + r % m) * 8 + b % 8;
-  return *rb >= 0;
+  const int m = min(per_set, NP / 8 - set * per_set), odd = m | 1;  // pairs of this set
+  *rb = max_blocks - 1 - r / odd;
+  *pair = (set * per_set + r % odd) * 8 + b % 8;
+  return *rb >= 0 && r % odd < m;
 }
 
 // The one-launch prefill writes a prompt's K/V rows into the group's prefix
@@ -442,7 +457,7 @@ __device__ __forceinline__ void pf_compute(const uint16_t* kst, int u0, float qk
 // VGPRs), two row tiles three (168 VGPRs).
 template <int D, int NREP, int RT, PfPages WP>
 __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(RT == 1 ? 4 : 3, 8)))
-void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride) {
+void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride, int per_set) {
   using L = PfSmem<D>;
   constexpr int KB = D / 32;              // MFMA k-blocks over head_dim
   constexpr int DT = D / 16;              // 16-column output tiles
@@ -455,7 +470,7 @@ void prefill_attn_kernel(const PrefillArgs a, int max_blocks, int stride) {
   const int Hkv = a.num_kv_heads, Hq = a.num_q_heads;
   const int NP = a.num_groups * Hkv;
   int pair, rb;
-  if (!pf_unit((int)blockIdx.x, NP, max_blocks, stride, &pair, &rb)) return;
+  if (!pf_unit((int)blockIdx.x, NP, max_blocks, stride, per_set, &pair, &rb)) return;
   const int g = pair / Hkv, h = pair - g * Hkv;
   int first;
   const int P = prompt_len(a, g, &first);
@@ -576,23 +591,30 @@ hipError_t attn_launch(const PrefillArgs& a, hipStream_t st) {
   const int max_blocks = cdiv(max_tokens, tpb);
   // A launch has at most 2^24 workgroups of 256 threads; the idle ones of the
   // ordered grid must not be what exceeds it.
-  const bool ordered =
-      NP % 8 == 0 && NP * max_blocks > pf_small_grid(D) && NP * (max_blocks + 1) < (1ll << 24);
-  const int stride = ordered ? pf_stride(max_blocks) : 0;
-  const long long pairs = NP / 8;
-  const long long blocks =
-      stride == 0 ? NP * max_blocks : 8 * (pairs / kPfPairs * stride + pairs % kPfPairs * max_blocks);
+  int stride = 0, per_set = 0;
+  long long blocks = NP * max_blocks;
+  const long long pairs = NP / 8;  // of an XCD
+  if (NP % 8 == 0 && blocks > pf_small_grid(pairs, D)) {
+    const int n = pf_set_pairs(pairs, (long long)a.num_tokens * a.num_kv_heads * D * 4);
+    const long long step = ((long long)(n | 1) * max_blocks) | 1, rest = pairs % n;
+    const long long with_idle = 8 * (pairs / n * step + (rest == 0 ? 0 : rest | 1) * max_blocks);
+    if (with_idle < (1ll << 24)) {
+      per_set = n;
+      stride = (int)step;
+      blocks = with_idle;
+    }
+  }
   if (blocks <= 0) return hipSuccess;
   const dim3 grid((unsigned)blocks), block(kPfThreads);
   if (a.write_pages && a.k_scale != nullptr) {
-    if (rt == 2) prefill_attn_kernel<D, NREP, 2, kPagesFp8><<<grid, block, 0, st>>>(a, max_blocks, stride);
-    else prefill_attn_kernel<D, NREP, 1, kPagesFp8><<<grid, block, 0, st>>>(a, max_blocks, stride);
+    if (rt == 2) prefill_attn_kernel<D, NREP, 2, kPagesFp8><<<grid, block, 0, st>>>(a, max_blocks, stride, per_set);
+    else prefill_attn_kernel<D, NREP, 1, kPagesFp8><<<grid, block, 0, st>>>(a, max_blocks, stride, per_set);
   } else if (a.write_pages) {
-    if (rt == 2) prefill_attn_kernel<D, NREP, 2, kPagesBf16><<<grid, block, 0, st>>>(a, max_blocks, stride);
-    else prefill_attn_kernel<D, NREP, 1, kPagesBf16><<<grid, block, 0, st>>>(a, max_blocks, stride);
+    if (rt == 2) prefill_attn_kernel<D, NREP, 2, kPagesBf16><<<grid, block, 0, st>>>(a, max_blocks, stride, per_set);
+    else prefill_attn_kernel<D, NREP, 1, kPagesBf16><<<grid, block, 0, st>>>(a, max_blocks, stride, per_set);
   } else {
-    if (rt == 2) prefill_attn_kernel<D, NREP, 2, kPagesNone><<<grid, block, 0, st>>>(a, max_blocks, stride);
-    else prefill_attn_kernel<D, NREP, 1, kPagesNone><<<grid, block, 0, st>>>(a, max_blocks, stride);
+    if (rt == 2) prefill_attn_kernel<D, NREP, 2, kPagesNone><<<grid, block, 0, st>>>(a, max_blocks, stride, per_set);
+    else prefill_attn_kernel<D, NREP, 1, kPagesNone><<<grid, block, 0, st>>>(a, max_blocks, stride, per_set);
   }
   return hipGetLastError();
 }

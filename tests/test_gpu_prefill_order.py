@@ -1,6 +1,6 @@
 """Prefill grids: the order that keeps few (group, kv-head) pairs on an XCD at a time, its remainders, and
-the plain order of small grids (up to 1024 workgroups, 2048 with 64-wide heads) and of pair counts that
-are no multiple of 8; prompts around the ends of key blocks and workgroup rows, one and two row tiles per
+the plain order of small grids (up to 1024 workgroups, 2048 with 64-wide heads and more than 16 pairs an
+XCD) and of pair counts that are no multiple of 8; prompts around the ends of key blocks and workgroup rows, one and two row tiles per
 wave. Every row is compared with the oracle."""
 import numpy as np
 import pytest
@@ -17,12 +17,20 @@ CASES = [
     ("two-sets-odd-blocks", 16, 8, 64, [95, 1, 32, 65, 96, 17], "bf16"),
     ("two-sets-even-blocks", 8, 8, 128, [128, 127, 0, 63, 64, 3, 100], "bf16"),
     ("half-pairs", 16, 4, 128, [40, 16, 70, 8], "fp8"),
-    # Ordered grids: sets of 5 of an XCD's pairs, with a remainder or none, odd and even row blocks.
+    # Ordered grids: one set of an XCD's pairs (at most 16, K and V up to 24 MiB), with an idle slot where they
+    # are even; sets of 5 otherwise, with every remainder, odd and even row blocks.
     ("ordered-one-set", 64, 8, 128, [345, 337, 344], "bf16"),             # 3 pairs per XCD, 44 row blocks
-    ("ordered-odd-blocks", 32, 8, 128, [5, 17, 33, 40, 0, 16] * 8, "bf16"),  # 48 pairs, 3 row blocks
-    ("ordered-even-blocks", 16, 8, 64, [61, 1, 32, 64, 33] * 26, "bf16"),  # 130 pairs, no remainder
-    ("ordered-fp8", 32, 4, 128, [40, 16, 70, 8] * 8, "fp8"),              # 16 pairs, 10 row blocks
-    ("ordered-two-tiles", 64, 8, 64, [385, 641, 400, 150, 700, 390], "bf16"),
+    ("ordered-one-even-set", 32, 4, 128, [40, 16, 70, 8] * 8, "fp8"),     # 16 pairs, 10 row blocks
+    ("ordered-two-tiles", 64, 8, 64, [385, 641, 400, 150, 700, 390], "bf16"),  # 6 pairs
+    ("ordered-large-rest-1", 32, 8, 128, [1040, 1040, 1041, 1030, 1040, 1000], "bf16"),  # 6 pairs, above 24 MiB
+    ("ordered-large-rest-4", 32, 8, 128, [700, 650, 697, 690, 690, 680, 701, 700, 690], "bf16"),  # 9 pairs
+    ("ordered-rest-0", 16, 8, 64, [61, 1, 32, 64, 33] * 26, "bf16"),      # 130 pairs, 2 row blocks
+    ("ordered-rest-2", 32, 8, 128, [128, 5, 64, 90] * 4 + [100], "bf16"),  # 17 pairs, 8 row blocks
+    ("ordered-rest-3", 32, 8, 128, [5, 17, 33, 40, 0, 16] * 8, "bf16"),   # 48 pairs, 3 row blocks
+    ("ordered-rest-4", 32, 8, 128, [112, 5, 64, 90] * 4 + [100, 3, 31], "fp8"),  # 19 pairs, 7 row blocks
+    ("few-d64-plain", 32, 8, 64, [255, 240, 256, 249, 13], "bf16"),     # 5 pairs, 640: plain
+    ("few-d64-over-the-line", 64, 8, 64, [255, 240, 256, 249, 13], "bf16"),  # 1280: one set
+    ("many-d64-at-the-line", 8, 8, 64, [127, 65, 63, 0] * 32, "bf16"),    # 128 pairs, 2048: plain
     ("at-the-line", 8, 8, 128, [64, 63, 17, 0] * 32, "bf16"),             # 1024 workgroups: plain
     ("over-the-line", 8, 8, 128, [65, 63, 17, 0] * 17, "bf16"),           # 1088
     ("plain-order", 4, 2, 128, [50, 33, 130], "bf16"),                   # 6 pairs
