@@ -228,7 +228,12 @@ bool small_batch(const Shape& sh) {
   const long long steps = (pages + per_step - 1) / per_step, kv_bytes = pages * sh.S * sh.Hkv * page_bytes;
   if (sh.S > rp::kSmallPlanMaxSeqs || steps > (sh.nrep >= 4 ? 20 : 10) || kv_bytes > (128ll << 20)) return false;
   const bool wide = sh.D == 128;
-  const int passes = rp::cdiv(sh.nrep * rp::cdiv(sh.S, sh.G), 16);  // over the prefix of a group of average size
+  // Passes over a group's prefix; several groups are seldom of one size, and
+  // from four query rows a member on, one member more is often a pass more (4
+  // sequences, 3 of them of one group, Hq 16, Hkv 2: three launches 24.0 us,
+  // one 18.0).
+  const int members = rp::cdiv(sh.S, sh.G) + (sh.G > 1 && sh.nrep >= 4 ? 1 : 0);
+  const int passes = rp::cdiv(sh.nrep * members, 16);
   const double one_us = (double)steps * (!sh.fp8 ? 1.0 : wide ? 1.15 : 1.55);
   const double three_us = (!wide ? 8.0 : sh.fp8 ? 9.0 : 10.0) + 0.05 * (double)kv_bytes / (1 << 20) +
                           (passes - 1) * std::min(sh.max_pp, rp::kPrefixChunkPages) * (wide ? 0.45 : 0.25);
