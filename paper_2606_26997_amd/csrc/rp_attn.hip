@@ -392,9 +392,12 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
 // query rows of the group's live members, 16 rows per pass. A group with more
 // than 16 query rows reads the chunk again for each further pass; the chunk
 // (128 KiB of K and V with 128-wide bf16 heads, half of that with 64-wide or fp8
-// ones) is then mostly in this XCD's L2, its V too, since prefix units load it
-// without the non-temporal hint (64 rows a group, Hq 32, Hkv 4, 256 sequences:
-// 395.9 us a step with the hint, 392.2 without; 16 rows 367 both ways).
+// ones) is then mostly in this XCD's L2, its V too, which is loaded without the
+// non-temporal hint then (64 rows a group, Hq 32, Hkv 4, 256 sequences: 395.9 us a
+// step with the hint, 392.2 without). One pass reads its V once, as a response
+// does, and takes the hint with 128-wide bf16 heads (101 sequences of one prompt
+// each, of 453-887 tokens, and responses of 229-1148 at Hq 8, Hkv 8: 113 us without
+// the hint, 98 with; other heads 0-2% slower with it).
 template <int D, int NREP, bool FP8>
 __device__ void prefix_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
   const int2 it = a.view.prefix_items[item];
@@ -418,8 +421,15 @@ __device__ void prefix_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
       qrow = static_cast<const uint16_t*>(a.q) + (size_t)rowid * D;
       part = clamp_part(rowid * a.view.parts_per_row + c, a.view.max_parts);
     }
-    attend_pages<D, FP8, 1, true>(a, h, bt, cdiv(ntok, kPage), ntok, qrow, 0, a.view.part_o + (size_t)part * D,
-                                  a.view.part_lse + part, vt);
+    float *po = a.view.part_o + (size_t)part * D, *pl = a.view.part_lse + part;
+    const int npages = cdiv(ntok, kPage);
+    if constexpr (D == 128 && !FP8) {
+      if (R <= 16) {
+        attend_pages<D, FP8, 1, false>(a, h, bt, npages, ntok, qrow, 0, po, pl, vt);
+        return;
+      }
+    }
+    attend_pages<D, FP8, 1, true>(a, h, bt, npages, ntok, qrow, 0, po, pl, vt);
   }
 }
 
