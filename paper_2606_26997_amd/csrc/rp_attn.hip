@@ -395,11 +395,19 @@ __device__ __forceinline__ bool attend_pages(const AttnArgs& a, int h, const int
 // ones) is then mostly in this XCD's L2, its V too, which is loaded without the
 // non-temporal hint then (64 rows a group, Hq 32, Hkv 4, 256 sequences: 395.9 us a
 // step with the hint, 392.2 without). One pass reads its V once, as a response
-// does, and takes the hint with 128-wide bf16 heads (101 sequences of one prompt
-// each, of 453-887 tokens, and responses of 229-1148 at Hq 8, Hkv 8: 113 us without
-// the hint, 98 with; other heads 0-2% slower with it).
+// does, and takes the hint where all prefixes together (`units`, full chunks of
+// every kv-head) reach 128 MiB, half of the last-level cache: less stays in that
+// from step to step, and the hint gives it up. Prompts of 500-1000 tokens, responses
+// of 20-200, Hkv 8, Hq 16, us without the hint and with it: 128-wide bf16, 120
+// prompts of 3 sequences each (280 MiB) 123 and 106; 64-wide bf16, 200 of 3 (230
+// MiB), 107 and 88; 128-wide fp8, the same, 110 and 92. Below the line, Hq 4, Hkv 2,
+// 50 of 4: 128-wide bf16 25.3 without, 27.2 with; 64-wide bf16 19.3 and 20.3.
+// Both forms inside one loop take 135 registers with 128-wide bf16 heads, three
+// waves per SIMD; one loop each takes 126, four waves, which long batches gain 0-0.5%
+// by and short groups of many passes lose 10% (8 prompts of 512-1024, 16 sequences
+// each, Hq 16, Hkv 2: 71 us and 81).
 template <int D, int NREP, bool FP8>
-__device__ void prefix_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
+__device__ void prefix_unit(const AttnArgs& a, int item, int h, int units, uint16_t* vt) {
   const int2 it = a.view.prefix_items[item];
   const int g = clamp_group(it.x, a.num_groups);
   const int c = min(max(it.y, 0), a.view.max_prefix_chunks - 1);
@@ -409,6 +417,7 @@ __device__ void prefix_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
   const int moff = a.view.grp_off[g];
   const int R = (a.view.grp_off[g + 1] - moff) * NREP;
   const int* bt = a.prefix_block_table + (size_t)g * a.max_prefix_pages + c * kPrefixChunkPages;
+  constexpr int kStreamUnits = (128 << 20) / (kPrefixChunkPages * 2 * Geom<D, FP8>::BLOCK_BYTES);
   const int r16 = threadIdx.x & 15;
   for (int r0 = 0; r0 < R; r0 += 16) {
     const int rr = r0 + r16;
@@ -423,11 +432,9 @@ __device__ void prefix_unit(const AttnArgs& a, int item, int h, uint16_t* vt) {
     }
     float *po = a.view.part_o + (size_t)part * D, *pl = a.view.part_lse + part;
     const int npages = cdiv(ntok, kPage);
-    if constexpr (D == 128 && !FP8) {
-      if (R <= 16) {
-        attend_pages<D, FP8, 1, false>(a, h, bt, npages, ntok, qrow, 0, po, pl, vt);
-        return;
-      }
+    if (R <= 16 && units >= kStreamUnits) {
+      attend_pages<D, FP8, 1, false>(a, h, bt, npages, ntok, qrow, 0, po, pl, vt);
+      return;
     }
     attend_pages<D, FP8, 1, true>(a, h, bt, npages, ntok, qrow, 0, po, pl, vt);
   }
@@ -487,7 +494,7 @@ void attn_parts_kernel(const AttnArgs a) {
   const int b = blockIdx.x;
   if (b < n_pre) {
     const int item = b / Hkv;
-    prefix_unit<D, NREP, FP8>(a, item, b - item * Hkv, vt);
+    prefix_unit<D, NREP, FP8>(a, item, b - item * Hkv, n_pre, vt);
     return;
   }
   const int resp = b - n_pre;

@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import oracle
+from gpu_util import compare, run_hip, run_oracle
 from workloads import make_workload
 
 pytestmark = pytest.mark.gpu
@@ -215,3 +216,21 @@ def test_combine_after_the_one_call_gives_its_results_again(case):
     assert torch.equal(torch.isnan(out), torch.isnan(b.out))
     assert torch.equal(out.nan_to_num(9.0).view(torch.int16), b.out.nan_to_num(9.0).view(torch.int16))
     assert torch.equal(lse.view(torch.int32), b.lse.view(torch.int32))
+
+
+@pytest.mark.parametrize("below", [False, True], ids=["at-the-line", "below"])
+@pytest.mark.parametrize("nrep,d,dt", [(1, 128, "bf16"), (2, 64, "bf16"), (4, 128, "fp8"), (8, 64, "fp8")])
+def test_prefix_units_at_the_line_of_the_streaming_hint(nrep, d, dt, below):
+    """128 MiB of prefixes in full chunks of 256 tokens, and one chunk less; one group of two passes."""
+    print(f"[case] prefix stream line nrep {nrep} d {d} {dt} below {below}", flush=True)
+    hkv = 8
+    groups = (128 << 20) // (4 * 256 * hkv * 2 * d * (2 if dt == "bf16" else 1))  # 4 chunks each
+    lens = [1024 - (37 * g) % 200 for g in range(groups)]
+    if below:
+        lens[-1] = 700
+    members = [0] * (16 // nrep) + list(range(groups))
+    wl = make_workload(num_q_heads=hkv * nrep, num_kv_heads=hkv, head_dim=d, seq_to_group=members, prefix_lens=lens,
+                       resp_lens=[(5 * i) % 40 for i in range(len(members))], seed=d + nrep, kv_dtype=dt)
+    _, out, lse = run_hip(wl, staged=True)
+    ref, ref_lse, _ = run_oracle(wl)
+    compare(out, lse, ref, ref_lse, dt)
