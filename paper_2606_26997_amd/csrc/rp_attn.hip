@@ -523,11 +523,12 @@ void attn_parts_kernel(const AttnArgs a) {
 // pages without it are 1-7% faster where one large group shares a long prefix
 // (64 sequences of 900 + 200 tokens, 2 kv-heads: 17.4 -> 16.6 us), and 1-4%
 // slower where several groups of 16 have as much response (4 x 16 of 300 + 300,
-// 4 kv-heads 13.6 -> 14.0). Block 0 makes the
-// batch's plan, as the three-launch form leaves it in the workspace, and a
-// row's merged result becomes its first partial there (the others empty), so
-// that a combine on the workspace gives out and lse again. Bound by the chain of round trips and steps of one wave (4 sequences of 192 tokens, 2
-// kv-heads: 8.2 us a call, three launches 13.2; the partials are 0.1 us of it).
+// 4 kv-heads 13.6 -> 14.0). Block 0 makes the batch's plan, as the three-launch
+// form leaves it in the workspace, and a row's merged result becomes its first
+// partial there (the others empty), so that a combine on the workspace gives out
+// and lse again. Bound by the chain of round trips and steps of one wave (4
+// sequences of 192 tokens, 2 kv-heads: 8.2 us a call, three launches 13.2; the
+// partials are 0.1 us of it).
 template <int D, int NREP, bool FP8>
 __global__ __launch_bounds__(64 * kSmallWaves) void attn_small_kernel(const AttnArgs a, const PlanArgs p, uint16_t* out,
                                                                       float* lse_out) {

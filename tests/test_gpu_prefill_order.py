@@ -1,7 +1,7 @@
 """Prefill grids: the order that keeps few (group, kv-head) pairs on an XCD at a time, its remainders, and
 the plain order of small grids (up to 1024 workgroups, 2048 with 64-wide heads and more than 16 pairs an
-XCD) and of pair counts that are no multiple of 8; prompts around the ends of key blocks and workgroup rows, one and two row tiles per
-wave. Every row is compared with the oracle."""
+XCD) and of pair counts that are no multiple of 8; prompts around the ends of key blocks and workgroup rows,
+one and two row tiles per wave. Every row is compared with the oracle."""
 import numpy as np
 import pytest
 import torch
